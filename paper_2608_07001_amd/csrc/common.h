@@ -82,22 +82,21 @@ struct TreeView {
   const uint8_t* fl_pre_add;  // [unit_cap] 1: the floor executed the unit's Add
   const uint8_t* fl_pre_sp;   // [node_cap] 1: the floor executed the node's Split
   const int64_t* fl_state;  // [8] B_floor first
-  // level-by-level refinement (bf16): items [lv_cap][8] as in work (the slot
-  // length word also holds the node's BFS index << 16, the Add key word the key
-  // of the op that creates the node), results [lv_cap][12], two lists of the
-  // units with nodes at the current depth, per unit (first, end, item base,
-  // items) of that depth, and counters
-  int32_t* lv_items;
-  int32_t* lv_res;
-  int32_t* lv_units;    // [2][unit_cap]
-  int4* lv_state;       // [unit_cap]
-  int32_t* lv_ctr;      // [16]
-  int64_t lv_cap;
+  // refinement below the roots (bf16): items of 8 int32 -- unit, absolute start,
+  // length | depth << 8 | node slot << 16, D, R, w (float bits), the utility
+  // bound of the op that creates the node
+  int32_t* long_items[2];   // nodes of more than ST_N tokens: this round's, the next round's
+  int64_t long_cap;
+  int32_t* sub_items;   // [LG][short_capacity] nodes of 2 .. ST_N tokens
+  int32_t* sub_ctr;     // [LG] their number
+  int32_t* lv_ctr;      // [16] [r] long nodes of round r, [8 + r] next item of round r
 };
-// bytes of the level region at the end of the tree buffer, and its item capacity
-// (the nodes of one depth are disjoint, at least two tokens each: N_c / 2 per (l, g))
+constexpr int ST_N = 16;          // tokens of the longest subtree that one wave takes to its singletons
+constexpr int LONG_ROUNDS = 3;    // 127 tokens at most below a root, then 63, then 31
+// bytes of those lists, and their capacities: the nodes of a list are disjoint
 size_t level_region_bytes(int64_t LG, int64_t N_c, int64_t unit_cap);
-int64_t level_capacity(int64_t LG, int64_t N_c);
+int64_t long_capacity(int64_t LG, int64_t N_c);
+__host__ __device__ inline int64_t short_capacity(int64_t N_c) { return N_c / 2; }   // per (l, g)
 
 // The singleton floor's region of the tree buffer (alpha_floor > 0).  Public
 // part, each array 256-byte aligned in this order: int64 state[8] (B_floor,
@@ -151,14 +150,11 @@ struct MhView {
 // CONTINUE refines every unrefined node whose creating op reaches theta.
 // ROOT_FULL refines the root of every unit (the first level of the complete
 // build).  For bf16 caches the roots are refined by their own kernel
-// (launch_split_root) in ROOT_SPLIT and ROOT_FULL, and the next levels by the
-// same kernel one depth at a time: LEVEL (pruned) and LEVEL_FULL (complete)
-// take the nodes of one depth from a list and write one result per node, which
-// the level pass then numbers in BFS order.
-enum { BUILD_FULL = 0, BUILD_ROOT_SPLIT = 2, BUILD_CONTINUE = 3, BUILD_ROOT_FULL = 4, BUILD_LEVEL = 5,
-       BUILD_LEVEL_FULL = 6 };
-constexpr int LEVELS_MAX = 48;   // depths refined level by level; deeper nodes go to the per-unit kernel
-constexpr int LEVELS_SPARSE = 12; // the same at a compression of 64x or more
+// (launch_split_root) in ROOT_SPLIT and ROOT_FULL, and below them by the same
+// kernel (LONG, pruned, and LONG_FULL, complete) and the subtree kernel
+// (subtree.hip).
+enum { BUILD_FULL = 0, BUILD_ROOT_SPLIT = 2, BUILD_CONTINUE = 3, BUILD_ROOT_FULL = 4, BUILD_LONG = 5,
+       BUILD_LONG_FULL = 6 };
 
 // ---- gains, utilities and keys (shared by the build and score kernels so that
 // both produce bit-identical keys) -------------------------------------------
@@ -191,6 +187,28 @@ __device__ __forceinline__ int round_half_even_mid(int x0, int x1) {
   return (h & 1) ? h + 1 : h;
 }
 
+// status word of the tree buffer: [0] latched fault bits, [1] the marker
+// gracekv_build_trees writes first
+constexpr int32_t STATUS_NUMERIC = 1, STATUS_PARTITION = 2, STATUS_CAPACITY = 4;
+constexpr int32_t STATUS_BUILT = 0x4b56424c;
+
+// a node to refine, appended to its list: round r's long nodes, or the subtrees of (l, g)
+__device__ __forceinline__ void push_node(const TreeView& tv, const Dims& dm, int r, int lg, int4 d0, int4 d1) {
+  int32_t* dst = nullptr;
+  if ((d0.z & 255) <= ST_N) {
+    const int pos = atomicAdd(&tv.sub_ctr[lg], 1);
+    const int64_t cap = short_capacity(dm.N_c);
+    if (pos < cap) dst = tv.sub_items + 8 * ((int64_t)lg * cap + pos);
+  } else {
+    const int pos = atomicAdd(&tv.lv_ctr[r], 1);
+    if (pos < tv.long_cap) dst = tv.long_items[r & 1] + 8 * (int64_t)pos;
+  }
+  // never: the nodes of a list are disjoint
+  if (!dst) { atomicOr(tv.status, STATUS_CAPACITY); return; }
+  ((int4*)dst)[0] = d0;
+  ((int4*)dst)[1] = d1;
+}
+
 Dims make_dims(const gracekv_config& c, const gracekv_plan& p);
 size_t decode_ws_bytes(const Dims& dm, int P);
 int decode_parts(const Dims& dm);
@@ -201,10 +219,6 @@ hipError_t launch_decode(const Dims& dm, const void* q, const int64_t* offsets, 
 hipError_t launch_decode_noalloc(const Dims& dm, const void* q, const int64_t* offsets, const void* K_out,
                                  const void* V_out, const float* logm_out, const void* K, const void* V, float* out,
                                  hipStream_t st);
-// status word of the tree buffer: [0] latched fault bits, [1] the marker
-// gracekv_build_trees writes first
-constexpr int32_t STATUS_NUMERIC = 1, STATUS_PARTITION = 2, STATUS_CAPACITY = 4;
-constexpr int32_t STATUS_BUILT = 0x4b56424c;
 constexpr size_t KARGS_BYTES = 1024;      // tail of the tree buffer: Dims at 0, TreeView at 512
 hipError_t launch_store_args(const Dims& dm, const TreeView& tv, hipStream_t st);
 // bf16 caches with at most 8 query heads per KV head: the direct relevance s-hat
@@ -423,11 +437,9 @@ hipError_t launch_root_bf16(const Dims& dm, const void* K, const void* V, const 
                             const float* sinT, const int32_t* slot_starts, const int32_t* n_slots, const TreeView& tv,
                             hipStream_t st);
 int root_bf16_lds_bytes(int d);
-// listed: the work list is already made (by the level passes); otherwise the
-// units with nodes to refine are listed first
 hipError_t launch_build(const Dims& dm, int lds_bytes, int mode, const void* K, const void* V, const void* Q,
                         const float* cosT, const float* sinT, const int32_t* slot_starts, const int32_t* n_slots,
-                        const float* kappa, const TreeView& tv, hipStream_t st, bool listed = false);
+                        const float* kappa, const TreeView& tv, hipStream_t st);
 hipError_t launch_omega(const Dims& dm, const float* omega_raw, const TreeView& tv, hipStream_t st);
 // rank: B_free - 1 (the cut) or B_free (the skip bound, also stored in theta[1])
 hipError_t launch_theta(const Dims& dm, const TreeView& tv, hipStream_t st, bool skip_bound);
@@ -448,14 +460,17 @@ int split_root_lds_bytes(int d);
 hipError_t launch_split_root(const Dims& dm, int mode, const void* K, const void* V, const void* Q, const float* cosT,
                              const float* sinT, const int32_t* slot_starts, const int32_t* n_slots, const float* kappa,
                              const TreeView& tv, int grid, hipStream_t st);
-// the levels below the roots (bf16): LEVELS_MAX (or LEVELS_SPARSE) rounds of the split kernel over
-// one depth's list and the level pass; full: the complete build
-hipError_t launch_levels(const Dims& dm, bool full, const void* K, const void* V, const void* Q, const float* cosT,
-                         const float* sinT, const int32_t* slot_starts, const int32_t* n_slots, const float* kappa,
-                         const TreeView& tv, int grid, hipStream_t st);
-hipError_t launch_levels_bf16(const Dims& dm, bool full, const void* K, const void* V, const void* Q,
+// everything below the roots (bf16): long nodes in LONG_ROUNDS launches of the
+// split kernel, subtrees of at most ST_N tokens, then the breadth-first order
+hipError_t launch_split_long(const Dims& dm, bool full, int round, const void* K, const void* V, const void* Q,
+                             const float* cosT, const float* sinT, const int32_t* slot_starts,
+                             const int32_t* n_slots, const float* kappa, const TreeView& tv, int grid,
+                             hipStream_t st);
+hipError_t launch_below_roots(const Dims& dm, bool full, const void* K, const void* V, const void* Q,
                               const float* cosT, const float* sinT, const int32_t* slot_starts,
-                              const int32_t* n_slots, const float* kappa, const TreeView& tv, hipStream_t st);
+                              const int32_t* n_slots, const float* kappa, const TreeView& tv, int cus,
+                              hipStream_t st);
+int device_cus();
 hipError_t selftest_mfma(int which, float* out, hipStream_t st);
 
 // Stage clock (GRACEKV_FLAG_STAGE_TIMES; stage ids GRACEKV_STAGE_*): clock_begin

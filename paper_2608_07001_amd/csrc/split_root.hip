@@ -1,15 +1,16 @@
-// First refinement level of the prototype trees (bf16 caches): the choice of
-// refinement for the root of every unit the build needs (App. A.3 "Recursive
+// Refinement of the long nodes of the prototype trees (bf16 caches): the root of
+// every unit the build needs, then the nodes of more than ST_N tokens below the
+// roots (App. A.3 "Recursive
 // refinement rule": eq:app_binary_split, eq:app_extract_split,
 // eq:app_split_choice; App. B.4 eq:app_tree_split_candidates), with the child
 // prototypes of eq:app_rope_prototype, eq:app_value_prototype,
 // eq:app_effective_multiplicity and their distortions eq:app_original_attention_stats
 // .. eq:app_node_and_drop_distortion.
 //
-// Every unit has exactly one node to refine here, so nothing of the unit has
-// to stay resident between nodes, and the workgroup is sized for two per CU
-// (256 threads, under 80 KB of LDS): while one workgroup waits at a barrier or
-// on memory, the other one computes.  Per unit:
+// A workgroup refines one node at a time, and nothing of the unit stays resident
+// between nodes; it is sized for two per CU (256 threads, under 80 KB of LDS):
+// while one workgroup waits at a barrier or on memory, the other one computes.
+// Per node:
 //   * candidates: curvature ranks of the positions t in [0, n-2] (cut t + 1),
 //     the midpoint, the extraction token (largest probe mass), all in local
 //     positions; prefix children [0, x) and suffix children [x, n);
@@ -36,7 +37,10 @@
 //     about 1e-6 of the node's attention mass in D, far below the distortions
 //     compared;
 //   * the fp32 scores decide (binary form wins ties, smaller cut wins ties)
-//     and the root and its children are written to the node table.
+//     and the node and its children are written to the node table.
+// Below the roots the workgroup goes on with the longest child of more than ST_N
+// tokens and lists the others (subtree.hip): a chain that peels one token at a
+// time ends in one launch instead of one per depth.
 #include "common.h"
 
 namespace gkv {
@@ -98,10 +102,11 @@ __device__ __forceinline__ void sr_split3(const float* x, u32x2& hi, u32x2& mid,
 __device__ __forceinline__ s16x4 sr_op(u32x2 v) { return __builtin_bit_cast(s16x4, v); }
 __device__ __forceinline__ int uni(int v) { return __builtin_amdgcn_readfirstlane(v); }
 
-// LV: a depth below the roots (the level list and results; mode BUILD_LEVEL or
-// BUILD_LEVEL_FULL), else the roots (mode BUILD_ROOT_SPLIT or BUILD_ROOT_FULL)
+// LV: the long nodes below the roots (mode BUILD_LONG or BUILD_LONG_FULL, one
+// round's list; the workgroup goes on with the longer long child of a node and
+// lists the others), else the roots (mode BUILD_ROOT_SPLIT or BUILD_ROOT_FULL)
 template <int D, bool LV>
-__global__ __launch_bounds__(SR_T, 2) void k_split_root(const Dims* __restrict__ dmp, int mode, int lvl,
+__global__ __launch_bounds__(SR_T, 2) void k_split_root(const Dims* __restrict__ dmp, int mode, int round,
                                                          const uint16_t* __restrict__ K,
                                                          const uint16_t* __restrict__ V,
                                                          const uint16_t* __restrict__ Q,
@@ -143,27 +148,27 @@ __global__ __launch_bounds__(SR_T, 2) void k_split_root(const Dims* __restrict__
   int* posL = XL + 96;                     // index of XB[k] in XL
   int* posR = XL + 128;                    // index of XB[k] in XR
   int* meta = XL + 160;                    // nl, nr, nb, p, kmin, kmax, index of p in XL, of p+1 in XR,
-                                           // forced extraction (singleton floor), work item
+                                           // forced extraction (singleton floor), work item, then (LV)
+                                           // whether a node follows in this workgroup, and that node:
+                                           // start, length | depth << 8 | node slot << 16, D, R, bound
   auto crow = [&](int r) { return sCs + r * SR_CC; };
 
   const int tid0 = threadIdx.x;
   const int J = *n_slots;
-  // roots: the build's work list; a level (depth lvl >= 1): that depth's list,
-  // its length in lv_ctr[lvl & 1], the next item in lv_ctr[2]
   constexpr bool level = LV;
-  const int32_t* items = level ? tv.lv_items : tv.work;
-  int32_t* next_ctr = level ? tv.lv_ctr + 2 : tv.wctr + 1;
-  const int nwork = level ? (int)min((int64_t)tv.lv_ctr[lvl & 1], tv.lv_cap) : tv.wctr[0];
-  if (level && blockIdx.x == 0 && tid0 == 0) {
-    // the counters the level pass after this kernel accumulates into: the next
-    // depth's items and units
-    tv.lv_ctr[(lvl + 1) & 1] = 0;
-    tv.lv_ctr[4 + ((lvl + 1) & 1)] = 0;
-  }
+  const int32_t* items = level ? tv.long_items[round & 1] : tv.work;
+  int32_t* next_ctr = level ? tv.lv_ctr + 8 + round : tv.wctr + 1;
+  const int nwork = level ? (int)min((int64_t)tv.lv_ctr[round], tv.long_cap) : tv.wctr[0];
+  const uint32_t thi = level && mode == BUILD_LONG ? (uint32_t)(tv.theta[0] >> 32) : 0u;
   const float scale = 1.0f / sqrtf((float)D);
   const float LOG2E = 1.44269504088896341f;
 
-  if (tid0 == 0) meta[9] = atomicAdd(next_ctr, 1);
+  if (tid0 == 0) {
+    meta[9] = atomicAdd(next_ctr, 1);
+    meta[10] = 0;
+  }
+  int64_t unit = 0;
+  float w = 0.f;
   for (;;) {
     // per-lane indices are formed inside the loop (values derived from them are
     // not held across items, which would not fit the register budget)
@@ -175,48 +180,99 @@ __global__ __launch_bounds__(SR_T, 2) void k_split_root(const Dims* __restrict__
     const bool pok = q < dm.W;
     sync_after_lds_stores();                 // meta[9] was stored at the end of the last pass
     const int wi = uni(meta[9]);
+    // a node of the same unit that the last pass left for this workgroup
+    const bool follows = level && uni(meta[10]) != 0;
+    int a0 = 0, word = 0;
+    float Dv = 0.f, Rroot = 0.f;
+    uint32_t bound = 0u;
+    uint64_t Eadd = 0ull;
+    if (follows) {
+      a0 = uni(meta[11]);
+      word = uni(meta[12]);
+      Dv = __int_as_float(uni(meta[13]));
+      Rroot = __int_as_float(uni(meta[14]));
+      bound = (uint32_t)uni(meta[15]);
+    }
     __syncthreads();
-    if (wi >= nwork) break;
+    if (!follows && wi >= nwork) break;
     // the next item, in flight while this one is processed (stored before the
     // barrier at the top of the next pass)
-    int wnext = 0;
-    if (tid == 0) wnext = atomicAdd(next_ctr, 1);
+    int wnext = wi;
+    if (!follows && tid == 0) wnext = atomicAdd(next_ctr, 1);
+    if (level && tid == 0) meta[10] = 0;
     auto publish_next = [&]() { if (tid == 0) meta[9] = wnext; };
     do {
-    // the work item: unit, the node's start, length (and BFS index), D and R, w
-    // and the key of the op that creates it (one load)
-    const int4 d0 = *(const int4*)(items + 8 * (int64_t)wi);
-    const int4 d1 = *(const int4*)(items + 8 * (int64_t)wi + 4);
-    const int64_t unit = uni(d0.x);
+    if (!follows) {
+      // the work item: unit, the node's start, length, D and R, w and the key (LV:
+      // the utility bound) of the op that creates it (one load)
+      const int4 d0 = *(const int4*)(items + 8 * (int64_t)wi);
+      const int4 d1 = *(const int4*)(items + 8 * (int64_t)wi + 4);
+      unit = uni(d0.x);
+      a0 = uni(d0.y);
+      word = uni(d0.z);
+      Dv = __int_as_float(uni(d0.w));
+      Rroot = __int_as_float(uni(d1.x));
+      w = __int_as_float(uni(d1.y));
+      bound = (uint32_t)uni(d1.z);
+      Eadd = mode == BUILD_ROOT_FULL ? 0ull : ((uint64_t)(uint32_t)uni(d1.w) << 32) | bound;
+    }
     const int lg = (int)(unit / dm.J_cap), j = (int)(unit % dm.J_cap);
     const int l = lg / dm.G, g = lg % dm.G;
-    const int a0 = uni(d0.y);
-    const int n = uni(d0.z) & 0xffff;
-    const float Dv = __int_as_float(uni(d0.w));
-    const float Rroot = __int_as_float(uni(d1.x));
-    const float w = __int_as_float(uni(d1.y));
-    const uint64_t Eadd = mode == BUILD_ROOT_FULL ? 0ull
-                                                  : ((uint64_t)(uint32_t)uni(d1.w) << 32) | (uint32_t)uni(d1.z);
+    const int n = word & 255;
     if (n < 2 || n > NMAX || j >= J) break;
     const int64_t base = (int64_t)lg * 2 * dm.N_c + 2 * (int64_t)a0;
     const uint32_t ord = (uint32_t)lg * (uint32_t)J + (uint32_t)j;
     const uint16_t* Kp = K + ((int64_t)lg * dm.T + a0) * D;
     const uint16_t* Vp = V + ((int64_t)lg * dm.T + a0) * D;
     const float* tokR = tv.tok_R + (int64_t)lg * dm.N_c + a0;
-    // ---- writes the root and its children (local positions), or a level's
-    // result: kind | nkid << 8 | cut << 16, U, then per child (start | length << 16),
-    // D, R (node-local positions; the level pass numbers and places them) ----
+    // ---- writes the root and its children (local positions; LV: the node's
+    // own choice, its children appended to the unit's nodes) ----
     auto write_tree = [&](int kind, int cut, int nkid, const int* ka, const int* kn, const float* kD,
                           const float* kR) {
       if constexpr (level) {
+        const int pos = atomicAdd(&tv.unit_nn[unit], nkid);
         float sd = 0.f;
         for (int k = 0; k < nkid; ++k) sd += kD[k];
         const float Us = utility(split_gain(w, Rroot, Dv, sd), nkid - 1);
-        int4* r = (int4*)(tv.lv_res + 12 * (int64_t)wi);
-        const int k2 = nkid > 2 ? ka[2] | (kn[2] << 16) : 0;
-        r[0] = make_int4(kind | (nkid << 8) | (cut << 16), __float_as_int(Us), ka[0] | (kn[0] << 16), ka[1] | (kn[1] << 16));
-        r[1] = make_int4(k2, __float_as_int(kD[0]), __float_as_int(kD[1]), nkid > 2 ? __float_as_int(kD[2]) : 0);
-        r[2] = make_int4(__float_as_int(kR[0]), __float_as_int(kR[1]), nkid > 2 ? __float_as_int(kR[2]) : 0, 0);
+        const uint32_t ub = min(bound, __float_as_uint(Us));
+        const bool pass = mode == BUILD_LONG_FULL || ub >= thi;
+        const int depth = (word >> 8) & 255;
+        const int sl = tv.slots[j], nslot = tv.slots[j + 1] - sl;
+        const int64_t ubase = (int64_t)lg * 2 * dm.N_c + 2 * (int64_t)sl;
+        int keep = -1, most = ST_N;          // the longest long child stays here
+        for (int k = 0; k < nkid; ++k)
+          if (pass && kn[k] > most) { keep = k; most = kn[k]; }
+        if (pos + nkid > 2 * nslot - 1) {    // a tree over n tokens has at most 2n - 1 nodes
+          atomicOr(tv.status, STATUS_CAPACITY);
+          return;
+        }
+        const int64_t s = ubase + ((word >> 16) & 255);
+        tv.node_nch[s] = (uint8_t)nkid;
+        tv.node_kind[s] = (uint8_t)kind;
+        tv.node_cut[s] = a0 + cut;
+        for (int k = 0; k < nkid; ++k) {
+          const int64_t c = ubase + pos + k;
+          tv.node_a[c] = a0 + ka[k];
+          tv.node_n[c] = kn[k];
+          tv.node_parent[c] = depth + 1;
+          tv.node_nch[c] = 0;
+          tv.node_kind[c] = 0;
+          tv.node_cut[c] = -1;
+          tv.node_D[c] = kD[k];
+          tv.node_R[c] = kR[k];
+          const int cw = kn[k] | ((depth + 1) << 8) | ((pos + k) << 16);
+          if (k == keep) {
+            meta[10] = 1;
+            meta[11] = a0 + ka[k];
+            meta[12] = cw;
+            meta[13] = __float_as_int(kD[k]);
+            meta[14] = __float_as_int(kR[k]);
+            meta[15] = (int)ub;
+          } else if (pass && kn[k] >= 2) {
+            push_node(tv, dm, round + 1, lg, make_int4((int)unit, a0 + ka[k], cw, __float_as_int(kD[k])),
+                      make_int4(__float_as_int(kR[k]), __float_as_int(w), (int)ub, 0));
+          }
+        }
         return;
       }
       tv.node_child[base] = 1;
@@ -229,7 +285,7 @@ __global__ __launch_bounds__(SR_T, 2) void k_split_root(const Dims* __restrict__
         tv.node_a[s] = a0 + ka[k];
         tv.node_n[s] = kn[k];
         tv.node_child[s] = -1;
-        tv.node_parent[s] = 0;
+        tv.node_parent[s] = 1;              // the depth: numbered at the end
         tv.node_nch[s] = 0;
         tv.node_kind[s] = 0;
         tv.node_cut[s] = -1;
@@ -1108,7 +1164,7 @@ __global__ __launch_bounds__(SR_T, 2) void k_split_root(const Dims* __restrict__
   }
 }
 
-static hipError_t launch_split(const Dims& dm, int mode, int lvl, const void* K, const void* V, const void* Q,
+static hipError_t launch_split(const Dims& dm, int mode, int round, const void* K, const void* V, const void* Q,
                                const float* cosT, const float* sinT, const int32_t* slot_starts,
                                const int32_t* n_slots, const float* kappa, const TreeView& tv, int grid,
                                hipStream_t st) {
@@ -1117,10 +1173,10 @@ static hipError_t launch_split(const Dims& dm, int mode, int lvl, const void* K,
   const TreeView* tvp = (const TreeView*)((const char*)tv.kargs + 512);
 #define GKV_SR(DD)                                                                                        \
   do {                                                                                                    \
-    auto fn = (mode == BUILD_LEVEL || mode == BUILD_LEVEL_FULL) ? k_split_root<DD, true> : k_split_root<DD, false>; \
+    auto fn = (mode == BUILD_LONG || mode == BUILD_LONG_FULL) ? k_split_root<DD, true> : k_split_root<DD, false>; \
     hipError_t e0 = hipFuncSetAttribute((const void*)fn, hipFuncAttributeMaxDynamicSharedMemorySize, lds); \
     if (e0 != hipSuccess) return e0;                                                                      \
-    hipLaunchKernelGGL(fn, dim3(grid), dim3(SR_T), lds, st, dmp, mode, lvl, (const uint16_t*)K,           \
+    hipLaunchKernelGGL(fn, dim3(grid), dim3(SR_T), lds, st, dmp, mode, round, (const uint16_t*)K,           \
                        (const uint16_t*)V, (const uint16_t*)Q, cosT, sinT, slot_starts, n_slots, kappa, tvp); \
   } while (0)
   if (dm.d == 128) GKV_SR(128); else if (dm.d == 64) GKV_SR(64); else return hipErrorInvalidValue;
@@ -1134,12 +1190,12 @@ hipError_t launch_split_root(const Dims& dm, int mode, const void* K, const void
   return launch_split(dm, mode, 0, K, V, Q, cosT, sinT, slot_starts, n_slots, kappa, tv, grid, st);
 }
 
-hipError_t launch_split_level(const Dims& dm, bool full, int lvl, const void* K, const void* V, const void* Q,
-                              const float* cosT, const float* sinT, const int32_t* slot_starts,
-                              const int32_t* n_slots, const float* kappa, const TreeView& tv, int grid,
-                              hipStream_t st) {
-  return launch_split(dm, full ? BUILD_LEVEL_FULL : BUILD_LEVEL, lvl, K, V, Q, cosT, sinT, slot_starts, n_slots,
-                      kappa, tv, grid, st);
+hipError_t launch_split_long(const Dims& dm, bool full, int round, const void* K, const void* V, const void* Q,
+                             const float* cosT, const float* sinT, const int32_t* slot_starts,
+                             const int32_t* n_slots, const float* kappa, const TreeView& tv, int grid,
+                             hipStream_t st) {
+  return launch_split(dm, full ? BUILD_LONG_FULL : BUILD_LONG, round, K, V, Q, cosT, sinT, slot_starts, n_slots, kappa,
+                      tv, grid, st);
 }
 
 }  // namespace gkv
