@@ -97,6 +97,7 @@ TreeView make_view(void* base, const gracekv_plan& p) {
   auto take = [&](size_t bytes) { char* q = lv + o; o = (o + bytes + 255) & ~(size_t)255; return q; };
   v.long_items[0] = (int32_t*)take((size_t)cap * 32);
   v.long_items[1] = (int32_t*)take((size_t)cap * 32);
+  v.long_items[2] = (int32_t*)take((size_t)cap * 32);
   v.long_cap = cap;
   v.sub_items = (int32_t*)take((size_t)(LG * short_capacity(p.N_c)) * 32);
   v.sub_ctr = (int32_t*)take((size_t)LG * 4);
@@ -276,7 +277,7 @@ gracekv_status gracekv_plan_sizes(const gracekv_config* c, gracekv_plan* p) {
   gracekv_plan tmp = *p;
   Dims dm = make_dims(*c, tmp);
   p->build_lds_bytes = build_lds_bytes(dm);
-  if (p->build_lds_bytes > 160 * 1024 || root_lds_bytes(dm) > 160 * 1024 || split_root_lds_bytes(c->d) > 80 * 1024)
+  if (p->build_lds_bytes > 160 * 1024 || root_lds_bytes(dm) > 160 * 1024 || split_lds_bytes(c->d) > 80 * 1024)
     return GRACEKV_ERR_UNSUPPORTED;
   const size_t NC = (size_t)p->node_cap, UC = (size_t)p->unit_cap;
   size_t o = 0;
@@ -432,8 +433,7 @@ gracekv_status gracekv_build_trees(const gracekv_config* c, const void* K, const
     const int clk = clock_begin(dm, roots ? GRACEKV_STAGE_ROOT_SPLIT : GRACEKV_STAGE_REFINE, st);
     const hipError_t e =
         !roots && dm.dtype == GRACEKV_BF16
-            ? launch_below_roots(dm, mode == BUILD_FULL, K, V, Q, rope_cos, rope_sin, slot_starts, n_slots, kappa, tv,
-                                 device_cus(), st)
+            ? launch_below_roots(dm, mode == BUILD_FULL, K, V, Q, rope_cos, rope_sin, n_slots, kappa, tv, device_cus(), st)
             : launch_build(dm, p.build_lds_bytes, mode, K, V, Q, rope_cos, rope_sin, slot_starts, n_slots, kappa, tv, st);
     clock_end(clk, st);
     return e;

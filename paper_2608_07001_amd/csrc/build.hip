@@ -888,23 +888,24 @@ __global__ __launch_bounds__(BT) void k_refine(const Dims* __restrict__ dmp, int
 
 // ---- work list: the units with a node to refine ---------------------------
 __global__ void k_work_reset(TreeView tv) {
-  if (threadIdx.x < 4) tv.wctr[threadIdx.x] = 0;
+  if (threadIdx.x < 16) tv.wctr[threadIdx.x] = 0;
 }
 
 // Lists the units to refine whose slot length lies in [n_lo, n_hi): the
 // launches go from long slots to short ones, so the persistent workgroups take
 // the long (slow) items first and finish together.
-__global__ void k_work_mark(Dims dm, int mode, TreeView tv, int n_lo, int n_hi) {
+// `len`: the index of the list length in wctr; `cls` (>= 0): the class whose end
+// the list has when the launch is done.
+__global__ void k_work_mark(Dims dm, int mode, TreeView tv, int n_lo, int n_hi, int len, int cls) {
   const int64_t unit = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (unit >= (int64_t)dm.L * dm.G * dm.J_cap) return;
-  const int lg = (int)(unit / dm.J_cap), j = (int)(unit % dm.J_cap);
+  const bool valid = unit < (int64_t)dm.L * dm.G * dm.J_cap;
+  const int lg = valid ? (int)(unit / dm.J_cap) : 0, j = valid ? (int)(unit % dm.J_cap) : 0;
   const int J = *tv.nslots;
-  if (j >= J || J > dm.J_cap) return;
-  const int64_t a0 = tv.slots[j];
-  const int ns = tv.slots[j + 1] - (int)a0;
-  if (ns < n_lo || ns >= n_hi) return;
+  const bool in = valid && j < J && J <= dm.J_cap;
+  const int64_t a0 = in ? tv.slots[j] : 0;
+  const int ns = in ? tv.slots[j + 1] - (int)a0 : -1;
   const int64_t base = (int64_t)lg * 2 * dm.N_c + 2 * a0;
-  const int nn = tv.unit_nn[unit];
+  const int nn = in && ns >= n_lo && ns < n_hi ? tv.unit_nn[unit] : 0;
   const uint64_t theta = (mode == BUILD_FULL || mode == BUILD_ROOT_FULL) ? 0ull : tv.theta[0];
   bool need = false;
   for (int i = 0; i < nn && !need; ++i) {
@@ -921,10 +922,20 @@ __global__ void k_work_mark(Dims dm, int mode, TreeView tv, int n_lo, int n_hi) 
       need = tv.sp_E[base + par] >= theta;
     }
   }
+  // one place in the list per wave
+  const uint64_t m = __ballot(need);
+  if (m == 0ull) return;
+  const int lane = threadIdx.x & 63;
+  int first = 0;
+  if (lane == __builtin_ctzll(m)) {
+    first = atomicAdd(&tv.wctr[len], __popcll(m));
+    if (cls >= 0) atomicMax(&tv.wctr[cls], first + __popcll(m));
+  }
+  first = __shfl(first, __builtin_ctzll(m), 64);
   if (need) {
     // the item carries what the refinement of the root reads first, so a
     // workgroup needs one load instead of a chain of dependent ones
-    const int pos = atomicAdd(&tv.wctr[0], 1);
+    const int pos = first + __popcll(m & ((1ull << lane) - 1ull));
     const uint64_t Ea = tv.add_E[unit];
     int4* it = (int4*)(tv.work + 8 * (int64_t)pos);
     it[0] = make_int4((int32_t)unit, (int32_t)a0, tv.node_n[base], __float_as_int(tv.node_D[base]));
@@ -951,12 +962,15 @@ hipError_t launch_build(const Dims& dm, int lds_bytes, int mode, const void* K, 
   const int64_t units = (int64_t)dm.L * dm.G * dm.J_cap;
   hipLaunchKernelGGL(k_work_reset, dim3(1), dim3(64), 0, st, tv);
   const unsigned mb = (unsigned)((units + 255) / 256);
-  hipLaunchKernelGGL(k_work_mark, dim3(mb), dim3(256), 0, st, dm, mode, tv, 96, NMAX + 1);
-  hipLaunchKernelGGL(k_work_mark, dim3(mb), dim3(256), 0, st, dm, mode, tv, 48, 96);
-  hipLaunchKernelGGL(k_work_mark, dim3(mb), dim3(256), 0, st, dm, mode, tv, 0, 48);
-  const bool roots = mode == BUILD_ROOT_SPLIT || mode == BUILD_ROOT_FULL;
-  if (dm.dtype == GRACEKV_BF16 && roots)
-    return launch_split_root(dm, mode, K, V, Q, cosT, sinT, slot_starts, n_slots, kappa, tv, 2 * device_cus(), st);
+  if (dm.dtype == GRACEKV_BF16) {           // the roots, by the classes of the split kernels
+    hipLaunchKernelGGL(k_work_mark, dim3(mb), dim3(256), 0, st, dm, mode, tv, NMAX / 2 + 1, NMAX + 1, 8, 0);
+    hipLaunchKernelGGL(k_work_mark, dim3(mb), dim3(256), 0, st, dm, mode, tv, NMAX / 4 + 1, NMAX / 2 + 1, 8, 1);
+    hipLaunchKernelGGL(k_work_mark, dim3(mb), dim3(256), 0, st, dm, mode, tv, 0, NMAX / 4 + 1, 8, 2);
+    return launch_split_roots(dm, mode, K, V, Q, cosT, sinT, n_slots, kappa, tv, device_cus(), st);
+  }
+  hipLaunchKernelGGL(k_work_mark, dim3(mb), dim3(256), 0, st, dm, mode, tv, 96, NMAX + 1, 0, -1);
+  hipLaunchKernelGGL(k_work_mark, dim3(mb), dim3(256), 0, st, dm, mode, tv, 48, 96, 0, -1);
+  hipLaunchKernelGGL(k_work_mark, dim3(mb), dim3(256), 0, st, dm, mode, tv, 0, 48, 0, -1);
   const dim3 grid((unsigned)device_cus());
 #define GKV_LAUNCH_REFINE(TT, DD)                                                                          \
   do {                                                                                                     \

@@ -13,6 +13,8 @@ constexpr int NMAX = 128;        // longest slot (n_max); units hold at most 2*N
 constexpr int NODE_MAX = 2 * NMAX - 1;
 constexpr int WMAX = 64;         // window queries
 constexpr int DMAX = 128;        // head dim
+constexpr int ST_N = 16;         // tokens of the longest subtree that one wave takes to its singletons
+constexpr int LONG_CLASSES = 3;  // longer nodes: up to 128, 64 and 32 tokens
 constexpr int CAND_MAX = 18;     // prefix (or suffix) children per refinement: 17 cuts + extraction side
 
 // Every size and hyperparameter a kernel needs, passed by value.
@@ -71,7 +73,8 @@ struct TreeView {
   void* selstate;       // radix-select state of that bound
   int32_t* work;        // [L*G*J_cap][8] work items: unit, slot start, slot length, and the root's
                         // D, R (float bits), the sensitivity w (float bits), the Add key (two words)
-  int32_t* wctr;        // [4] list length, next item
+  int32_t* wctr;        // [16] fp32: list length, next item; bf16: [c] end of length class c in the list
+                        // (0: empty), [4 + c] next item of it, [8] list length
   void* proto;          // [unit_cap][2][d] root prototype (k~, v~) of each unit, cache dtype
   float* proto_logm;    // [unit_cap] log m_eff of the root
   void* kargs;          // device copy of the kernel arguments (Dims, then this view) for the
@@ -85,14 +88,12 @@ struct TreeView {
   // refinement below the roots (bf16): items of 8 int32 -- unit, absolute start,
   // length | depth << 8 | node slot << 16, D, R, w (float bits), the utility
   // bound of the op that creates the node
-  int32_t* long_items[2];   // nodes of more than ST_N tokens: this round's, the next round's
+  int32_t* long_items[LONG_CLASSES];   // nodes of more than 64, 32 and ST_N tokens
   int64_t long_cap;
   int32_t* sub_items;   // [LG][short_capacity] nodes of 2 .. ST_N tokens
   int32_t* sub_ctr;     // [LG] their number
-  int32_t* lv_ctr;      // [16] [r] long nodes of round r, [8 + r] next item of round r
+  int32_t* lv_ctr;      // [16] [c] long nodes of class c, [8 + c] next item of class c
 };
-constexpr int ST_N = 16;          // tokens of the longest subtree that one wave takes to its singletons
-constexpr int LONG_ROUNDS = 3;    // 127 tokens at most below a root, then 63, then 31
 // bytes of those lists, and their capacities: the nodes of a list are disjoint
 size_t level_region_bytes(int64_t LG, int64_t N_c, int64_t unit_cap);
 int64_t long_capacity(int64_t LG, int64_t N_c);
@@ -150,7 +151,7 @@ struct MhView {
 // CONTINUE refines every unrefined node whose creating op reaches theta.
 // ROOT_FULL refines the root of every unit (the first level of the complete
 // build).  For bf16 caches the roots are refined by their own kernel
-// (launch_split_root) in ROOT_SPLIT and ROOT_FULL, and below them by the same
+// (launch_split_roots) in ROOT_SPLIT and ROOT_FULL, and below them by the same
 // kernel (LONG, pruned, and LONG_FULL, complete) and the subtree kernel
 // (subtree.hip).
 enum { BUILD_FULL = 0, BUILD_ROOT_SPLIT = 2, BUILD_CONTINUE = 3, BUILD_ROOT_FULL = 4, BUILD_LONG = 5,
@@ -192,16 +193,18 @@ __device__ __forceinline__ int round_half_even_mid(int x0, int x1) {
 constexpr int32_t STATUS_NUMERIC = 1, STATUS_PARTITION = 2, STATUS_CAPACITY = 4;
 constexpr int32_t STATUS_BUILT = 0x4b56424c;
 
-// a node to refine, appended to its list: round r's long nodes, or the subtrees of (l, g)
-__device__ __forceinline__ void push_node(const TreeView& tv, const Dims& dm, int r, int lg, int4 d0, int4 d1) {
+// a node to refine, appended to its list: one of the long classes, or the subtrees of (l, g)
+__device__ __forceinline__ void push_node(const TreeView& tv, const Dims& dm, int lg, int4 d0, int4 d1) {
   int32_t* dst = nullptr;
-  if ((d0.z & 255) <= ST_N) {
+  const int n = d0.z & 255;
+  if (n <= ST_N) {
     const int pos = atomicAdd(&tv.sub_ctr[lg], 1);
     const int64_t cap = short_capacity(dm.N_c);
     if (pos < cap) dst = tv.sub_items + 8 * ((int64_t)lg * cap + pos);
   } else {
-    const int pos = atomicAdd(&tv.lv_ctr[r], 1);
-    if (pos < tv.long_cap) dst = tv.long_items[r & 1] + 8 * (int64_t)pos;
+    const int c = n > NMAX / 2 ? 0 : (n > NMAX / 4 ? 1 : 2);
+    const int pos = atomicAdd(&tv.lv_ctr[c], 1);
+    if (pos < tv.long_cap) dst = (c == 0 ? tv.long_items[0] : (c == 1 ? tv.long_items[1] : tv.long_items[2])) + 8 * (int64_t)pos;
   }
   // never: the nodes of a list are disjoint
   if (!dst) { atomicOr(tv.status, STATUS_CAPACITY); return; }
@@ -426,6 +429,46 @@ __device__ __forceinline__ f32x4 mfma_bf16_16x16x32(s16x8 a, s16x8 b, f32x4 c) {
                                                  0, 0);
 }
 
+// orders the wave's own LDS accesses (which the hardware keeps in order) for the compiler
+__device__ __forceinline__ void wave_lds_order() { asm volatile("" ::: "memory"); }
+
+// A product's result read by a vector instruction in another basic block: the
+// compiler pads the wait for the matrix pipeline along one of the two paths into
+// the block only (seen where a wave-uniform branch follows the products: the
+// reader ran two cycles after them and took old values).  The wait is stated
+// here, in the products' own block; it covers every product issued before.
+__device__ __forceinline__ void mfma_done(f32x4& x) { asm volatile("s_nop 15\n\ts_nop 4" : "+v"(x)); }
+template <int N>
+__device__ __forceinline__ void mfma_done(f32x4 (&x)[N]) {
+  mfma_done(x[0]);
+#pragma unroll
+  for (int i = 1; i < N; ++i) asm volatile("" : "+v"(x[i]));
+}
+
+// x[pt][r] (lane (i, g): row 4 g + r of a 16-row tile, column i of column tile
+// pt) -> y[4 h + r] at lane 16 pt + i: row 4 h + r of the wave's column
+__device__ __forceinline__ void tiles_to_columns(const f32x4* x, float* y) {
+#pragma unroll
+  for (int r = 0; r < 4; ++r) {
+    const auto p = __builtin_amdgcn_permlane32_swap(__float_as_uint(x[0][r]), __float_as_uint(x[2][r]), false, false);
+    const auto q = __builtin_amdgcn_permlane32_swap(__float_as_uint(x[1][r]), __float_as_uint(x[3][r]), false, false);
+    const auto s = __builtin_amdgcn_permlane16_swap(p[0], q[0], false, false);
+    const auto t = __builtin_amdgcn_permlane16_swap(p[1], q[1], false, false);
+    y[r] = __uint_as_float(s[0]);
+    y[4 + r] = __uint_as_float(s[1]);
+    y[8 + r] = __uint_as_float(t[0]);
+    y[12 + r] = __uint_as_float(t[1]);
+  }
+}
+
+// inclusive prefix sums along each 16-lane row
+__device__ __forceinline__ float row_scan16(float v) {
+  v += __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), 0x111, 0xf, 0xf, true));
+  v += __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), 0x112, 0xf, 0xf, true));
+  v += __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), 0x114, 0xf, 0xf, true));
+  v += __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), 0x118, 0xf, 0xf, true));
+  return v;
+}
 // ---- launchers (each defined in its own translation unit) -----------------
 hipError_t launch_rowstats(const Dims& dm, const void* K, const void* Q, const TreeView& tv, float4* partial,
                            hipStream_t st);
@@ -456,20 +499,18 @@ size_t select_ws_bytes(const Dims& dm);
 size_t pack_ws_bytes(const Dims& dm);
 int rowstats_chunks(const Dims& dm);
 int build_lds_bytes(const Dims& dm);
-int split_root_lds_bytes(int d);
-hipError_t launch_split_root(const Dims& dm, int mode, const void* K, const void* V, const void* Q, const float* cosT,
-                             const float* sinT, const int32_t* slot_starts, const int32_t* n_slots, const float* kappa,
-                             const TreeView& tv, int grid, hipStream_t st);
-// everything below the roots (bf16): long nodes in LONG_ROUNDS launches of the
-// split kernel, subtrees of at most ST_N tokens, then the breadth-first order
-hipError_t launch_split_long(const Dims& dm, bool full, int round, const void* K, const void* V, const void* Q,
-                             const float* cosT, const float* sinT, const int32_t* slot_starts,
-                             const int32_t* n_slots, const float* kappa, const TreeView& tv, int grid,
-                             hipStream_t st);
+int split_lds_bytes(int d);
+// bf16: the roots of the work list, and the long nodes below the roots
+hipError_t launch_split_roots(const Dims& dm, int mode, const void* K, const void* V, const void* Q, const float* cosT,
+                              const float* sinT, const int32_t* n_slots, const float* kappa, const TreeView& tv,
+                              int cus, hipStream_t st);
+hipError_t launch_split_long(const Dims& dm, bool full, const void* K, const void* V, const void* Q,
+                             const float* cosT, const float* sinT, const int32_t* n_slots, const float* kappa,
+                             const TreeView& tv, int cus, hipStream_t st);
+// everything below the roots (bf16): long nodes, subtrees of at most ST_N tokens, then the breadth-first order
 hipError_t launch_below_roots(const Dims& dm, bool full, const void* K, const void* V, const void* Q,
-                              const float* cosT, const float* sinT, const int32_t* slot_starts,
-                              const int32_t* n_slots, const float* kappa, const TreeView& tv, int cus,
-                              hipStream_t st);
+                              const float* cosT, const float* sinT, const int32_t* n_slots, const float* kappa,
+                              const TreeView& tv, int cus, hipStream_t st);
 int device_cus();
 hipError_t selftest_mfma(int which, float* out, hipStream_t st);
 

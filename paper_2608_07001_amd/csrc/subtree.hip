@@ -5,10 +5,9 @@
 // nodes are refined in any order and numbered at the end:
 //   * k_sub_first lists the children of the refined roots: nodes of more than
 //     ST_N tokens for the split kernel, smaller ones for the subtree kernel;
-//   * the split kernel (split_root.hip, its LV form) refines the long nodes, one
-//     workgroup per node; the workgroup goes on with the longer of the long
-//     children and lists the other, which has at most half the tokens: three
-//     launches end every chain (127 -> 63 -> 31 -> 15 tokens);
+//   * the split kernels (split.hip, their LV form) refine the long nodes, one
+//     workgroup per node, class by class (128, 64 and 32 tokens at most); a
+//     workgroup goes on with the child of its own class and lists the others;
 //   * k_subtree takes a node of at most ST_N tokens to its singletons, one wave
 //     per node, with no barrier;
 //   * k_number gives every unit its breadth-first order.
@@ -34,7 +33,7 @@ int64_t long_capacity(int64_t LG, int64_t N_c) { return LG * (N_c / (ST_N + 1)) 
 
 static size_t al256(size_t x) { return (x + 255) & ~(size_t)255; }
 
-// Two lists of long nodes, the subtrees, their counters and lv_ctr, 20 bytes a
+// Three lists of long nodes, the subtrees, their counters and lv_ctr, 22 bytes a
 // token; the region keeps the 40 that its interface version reserves.
 size_t level_region_bytes(int64_t LG, int64_t N_c, int64_t unit_cap) {
   const size_t cap = (size_t)(LG * (N_c / 2) + 1);
@@ -55,7 +54,7 @@ __global__ __launch_bounds__(256) void k_sub_first(const Dims* __restrict__ dmp,
                                                    int full) {
   const Dims& dm = *dmp;
   const TreeView& tv = *tvp;
-  const int nunits = tv.wctr[0];
+  const int nunits = tv.wctr[8];
   const int J = *tv.nslots;
   const uint64_t theta = full ? 0ull : tv.theta[0];
   for (int k = (int)(blockIdx.x * blockDim.x + threadIdx.x); k < nunits; k += (int)(gridDim.x * blockDim.x)) {
@@ -71,7 +70,7 @@ __global__ __launch_bounds__(256) void k_sub_first(const Dims* __restrict__ dmp,
     for (int c = 1; c < cnt; ++c) {
       const int n = tv.node_n[base + c];
       if (n < 2) continue;
-      push_node(tv, dm, 0, lg, make_int4(unit, tv.node_a[base + c], n | (1 << 8) | (c << 16),
+      push_node(tv, dm, lg, make_int4(unit, tv.node_a[base + c], n | (1 << 8) | (c << 16),
                                          __float_as_int(tv.node_D[base + c])),
                 make_int4(__float_as_int(tv.node_R[base + c]), __float_as_int(w), (int32_t)(Ef >> 32), 0));
     }
@@ -122,33 +121,6 @@ struct StLds {
 };
 static_assert(StLds<128>::bytes <= 80 * 1024, "two workgroups per CU");
 
-// orders the wave's own LDS accesses (which the hardware keeps in order) for the compiler
-__device__ __forceinline__ void wave_lds_order() { asm volatile("" ::: "memory"); }
-
-// x[pt][r] (lane (i, g): row 4 g + r of a 16-row tile, column i of column tile
-// pt) -> y[4 h + r] at lane 16 pt + i: row 4 h + r of the wave's column
-__device__ __forceinline__ void tiles_to_columns(const f32x4* x, float* y) {
-#pragma unroll
-  for (int r = 0; r < 4; ++r) {
-    const auto p = __builtin_amdgcn_permlane32_swap(__float_as_uint(x[0][r]), __float_as_uint(x[2][r]), false, false);
-    const auto q = __builtin_amdgcn_permlane32_swap(__float_as_uint(x[1][r]), __float_as_uint(x[3][r]), false, false);
-    const auto s = __builtin_amdgcn_permlane16_swap(p[0], q[0], false, false);
-    const auto t = __builtin_amdgcn_permlane16_swap(p[1], q[1], false, false);
-    y[r] = __uint_as_float(s[0]);
-    y[4 + r] = __uint_as_float(s[1]);
-    y[8 + r] = __uint_as_float(t[0]);
-    y[12 + r] = __uint_as_float(t[1]);
-  }
-}
-
-// inclusive prefix sums along each 16-lane row
-__device__ __forceinline__ float row_scan16(float v) {
-  v += __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), 0x111, 0xf, 0xf, true));
-  v += __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), 0x112, 0xf, 0xf, true));
-  v += __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), 0x114, 0xf, 0xf, true));
-  v += __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), 0x118, 0xf, 0xf, true));
-  return v;
-}
 // (value, index) of the largest value of each row, ties to the smaller index
 __device__ __forceinline__ void row_argmax(float& v, int& i) {
 #pragma unroll
@@ -179,7 +151,7 @@ __global__ __launch_bounds__(ST_T, 2) void k_subtree(const Dims* __restrict__ dm
   for (int e = threadIdx.x; e < ST_N * H2; e += ST_T)
     sTab[e] = e / H2 < dm.T ? make_float2(cosT[e], sinT[e]) : make_float2(1.f, 0.f);
   __syncthreads();
-  const int wave = uni((int)threadIdx.x >> 6), lane = threadIdx.x & 63, i16 = lane & 15, g4 = lane >> 4;
+  const int wave = uni((int)threadIdx.x >> 6);
   char* wb = smem + Lay::oWave + wave * Lay::wBytes;
   uint16_t* sK = (uint16_t*)(wb + Lay::wK);
   float* sG = (float*)(wb + Lay::wG);
@@ -188,11 +160,9 @@ __global__ __launch_bounds__(ST_T, 2) void k_subtree(const Dims* __restrict__ dm
   float2* sA = (float2*)(wb + Lay::wA);
   int4* sN = (int4*)(wb + Lay::wN);
   uint32_t* sU = (uint32_t*)(wb + Lay::wU);
-  const int pi = lane & (H2 - 1);                         // rotation pair of the lane
   const float sc2 = LOG2E / sqrtf((float)D);
   const float invW = 1.0f / (float)dm.W;
-  const float invn = 1.0f / (float)(i16 + 1);             // lane i: 1 / (i + 1)
-  const int npt = (dm.W + 15) >> 4;
+  const float invn = 1.0f / (float)((threadIdx.x & 15) + 1);   // lane i: 1 / (i + 1)
   const int LG = dm.L * dm.G;
   const uint32_t thi = full ? 0u : (uint32_t)(tv.theta[0] >> 32);
   const int nw = (int)gridDim.x * (ST_T / 64);
@@ -202,6 +172,11 @@ __global__ __launch_bounds__(ST_T, 2) void k_subtree(const Dims* __restrict__ dm
     const int i0 = (int)(cnt * ch / chunks), i1 = (int)(cnt * (ch + 1) / chunks);
     if (i0 >= i1) continue;
     const int l = lg / dm.G, g = lg % dm.G;
+    // per-lane indices are formed inside the loops: what the compiler derives from
+    // them would else be held across items, past the register budget
+    int lane = threadIdx.x & 63;
+    asm volatile("" : "+v"(lane));
+    const int i16 = lane & 15, g4 = lane >> 4;
     // probe rows as the products' column operand, probe shift and normaliser of probe `lane`
     uint4 qf[4][KS];
     {
@@ -219,6 +194,9 @@ __global__ __launch_bounds__(ST_T, 2) void k_subtree(const Dims* __restrict__ dm
     const float izc = lane < dm.W ? 1.0f / tv.probe_ZC[(int64_t)lg * dm.W + lane] : 0.f;
     const float w = tv.omega[lg];
     for (int it = i0; it < i1; ++it) {
+      int lane = threadIdx.x & 63;
+      asm volatile("" : "+v"(lane));
+      const int i16 = lane & 15, g4 = lane >> 4, pi = lane & (H2 - 1);   // pi: rotation pair
       const int4* ip = (const int4*)(tv.sub_items + 8 * ((int64_t)lg * short_capacity(dm.N_c) + it));
       const int4 d0 = ip[0], d1 = ip[1];
       const int unit = uni(d0.x), a0 = uni(d0.y), word = uni(d0.z);
@@ -255,11 +233,10 @@ __global__ __launch_bounds__(ST_T, 2) void k_subtree(const Dims* __restrict__ dm
 #pragma unroll
           for (int pt = 0; pt < 4; ++pt) {
             acc[pt] = f32x4{0.f, 0.f, 0.f, 0.f};
-            if (pt < npt) {
 #pragma unroll
-              for (int s = 0; s < KS; ++s) acc[pt] = mfma_bf16_16x16x32(pk8(kf[s]), pk8(qf[pt][s]), acc[pt]);
-            }
+            for (int s = 0; s < KS; ++s) acc[pt] = mfma_bf16_16x16x32(pk8(kf[s]), pk8(qf[pt][s]), acc[pt]);
           }
+          mfma_done(acc);
           tiles_to_columns(acc, e);
 #pragma unroll
           for (int t = 0; t < ST_N; ++t) e[t] = __builtin_amdgcn_exp2f(e[t] * sc2 - mq2);
@@ -270,6 +247,8 @@ __global__ __launch_bounds__(ST_T, 2) void k_subtree(const Dims* __restrict__ dm
           kk = mfma_bf16_16x16x32(pk8(kf[s]), pk8(kf[s]), kk);
           gg = mfma_bf16_16x16x32(pk8(vf[s]), pk8(vf[s]), gg);
         }
+        mfma_done(kk);
+        mfma_done(gg);
         // the diagonal of a tile sits at lane (i, i / 4), element i % 4; every row gets it
         const int rs = i16 & 3;
         auto diagonal = [&](const f32x4& x) {
@@ -371,12 +350,10 @@ __global__ __launch_bounds__(ST_T, 2) void k_subtree(const Dims* __restrict__ dm
                         kl = pk8(*(const uint4*)(src + 2 * ST_N * KPS));
 #pragma unroll
             for (int pt = 0; pt < 4; ++pt) {
-              if (pt < npt) {
-                const s16x8 qb = pk8(qf[pt][s]);
-                acc[pt] = mfma_bf16_16x16x32(kl, qb, acc[pt]);
-                acc[pt] = mfma_bf16_16x16x32(km, qb, acc[pt]);
-                acc[pt] = mfma_bf16_16x16x32(kh, qb, acc[pt]);
-              }
+              const s16x8 qb = pk8(qf[pt][s]);
+              acc[pt] = mfma_bf16_16x16x32(kl, qb, acc[pt]);
+              acc[pt] = mfma_bf16_16x16x32(km, qb, acc[pt]);
+              acc[pt] = mfma_bf16_16x16x32(kh, qb, acc[pt]);
             }
             nn2 = mfma_bf16_16x16x32(kl, kh, nn2);
             nn2 = mfma_bf16_16x16x32(kh, kl, nn2);
@@ -385,6 +362,8 @@ __global__ __launch_bounds__(ST_T, 2) void k_subtree(const Dims* __restrict__ dm
             nn2 = mfma_bf16_16x16x32(kh, km, nn2);
             nn2 = mfma_bf16_16x16x32(kh, kh, nn2);
           }
+          mfma_done(nn2);
+          mfma_done(acc);
           // constants of the child [a, t]: lane (t, t / 4) holds its key's norm
           {
             const float ss = rs == 0 ? nn2[0] : (rs == 1 ? nn2[1] : (rs == 2 ? nn2[2] : nn2[3]));
@@ -690,18 +669,15 @@ __global__ __launch_bounds__(256) void k_number(const Dims* __restrict__ dmp, co
 }
 
 hipError_t launch_below_roots(const Dims& dm, bool full, const void* K, const void* V, const void* Q,
-                              const float* cosT, const float* sinT, const int32_t* slot_starts,
-                              const int32_t* n_slots, const float* kappa, const TreeView& tv, int cus,
-                              hipStream_t st) {
+                              const float* cosT, const float* sinT, const int32_t* n_slots, const float* kappa,
+                              const TreeView& tv, int cus, hipStream_t st) {
   const Dims* dmp = (const Dims*)tv.kargs;
   const TreeView* tvp = (const TreeView*)((const char*)tv.kargs + 512);
   const int f = full ? 1 : 0;
   hipLaunchKernelGGL(k_sub_reset, dim3(1), dim3(256), 0, st, dmp, tvp);
   hipLaunchKernelGGL(k_sub_first, dim3((unsigned)(2 * cus)), dim3(256), 0, st, dmp, tvp, f);
-  for (int r = 0; r < LONG_ROUNDS; ++r) {
-    const hipError_t e = launch_split_long(dm, full, r, K, V, Q, cosT, sinT, slot_starts, n_slots, kappa, tv, 2 * cus, st);
-    if (e != hipSuccess) return e;
-  }
+  const hipError_t e = launch_split_long(dm, full, K, V, Q, cosT, sinT, n_slots, kappa, tv, cus, st);
+  if (e != hipSuccess) return e;
   // a wave takes a share of one (l, g)'s subtrees at a time (the probe rows stay
   // in registers): about eight shares per wave, dealt round the grid
   const int grid = 2 * cus, LG = dm.L * dm.G;
