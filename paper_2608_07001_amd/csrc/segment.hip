@@ -24,6 +24,7 @@
 //     depend only on F[< i], so 16 ends advance per step; ties go to the
 //     smallest predecessor; terminal relaxation eq:app_terminal_predecessor;
 //     backtrack from LDS.
+#include <algorithm>
 #include <climits>
 
 #include "common.h"
@@ -49,20 +50,26 @@ struct SegWs {
   void* rz;         // robust-z select state
   uint8_t* Poff;    // [N_c + 1] backpointer offsets i - P(i) (0: none)
   double* Fdbg;     // [4] F(N), chunks recomputed by the fix-up
-  double* S;        // [N_c][128] slot scores by (i, length), candidate-major per lane
+  double* S;        // [N_c][128] slot scores by (i, length), candidate-major per lane; then the same in fixed point
   long long* Fg;    // [C][DPC + 128] fixed-point F of positions c DPC - 127 .. (c + 1) DPC
   long long* dlt;   // [C] offset that turns Fg[c] into the true F
   long long* cdiff; // [C] constant difference Fg[c-1] - Fg[c] over chunk c's window
   int32_t* cok;     // [C] that difference is constant
   double* smax_part; // [N_c / SLE + 1] largest finite |S| per slot-score workgroup
-  int2* bt_tab;     // [C][128] backtrack: (exit, starts emitted) per chunk entry
-  int2* bt_ent;     // [C] (entry, output offset) of each chunk on the path
+  int2* bt_tab;     // [backtrack chunks][128] (exit, starts emitted) per chunk entry
+  int2* bt_ent;     // [backtrack chunks] (entry, output offset) of each chunk on the path
 };
 
 // Chunk-parallel DP: ends per chunk and the warm-up margin of a chunk's guessed run.
-constexpr int DPC = 1024;
-constexpr int DPM = 1024;
+// The run of a chunk is a serial chain of (DPC + margin) / 16 steps of about 1 us.
+constexpr int DPC = 512;
 __host__ __device__ inline int64_t dp_chunks(int64_t N) { return (N + DPC - 1) / DPC; }
+// One guess in a hundred is not settled after 512 ends and costs the fix-up 35 us
+// (1 to 3 of 256 chunks at 131 K); few chunks: the shorter warm-up is the better bet.
+__host__ __device__ inline int64_t dp_margin(int64_t N) { return dp_chunks(N) > 64 ? 1024 : 512; }
+// Chunks of the backtrack: one thread chains them, a dependent load (0.3 us) each.
+constexpr int BTC = 4096;
+__host__ __device__ inline int64_t bt_chunks(int64_t N) { return (N + BTC - 1) / BTC; }
 
 static size_t al(size_t x) { return (x + 255) & ~(size_t)255; }
 
@@ -281,7 +288,44 @@ struct RzState {
   uint32_t done[2];
   uint32_t hist[2][256];
 };
-constexpr int RZ_WG = 128;      // workgroups per select and pass
+// workgroups per select and pass: 4096 values each (their 256 bins meet in global atomics)
+static unsigned rz_workgroups(int64_t T) { return (unsigned)std::min<int64_t>((T + 4095) / 4096, 128); }
+
+// The bin of h (256 counts, ascending) that holds `rank`, by one wave: the lane
+// that finds it gets the counts before it in `before`, the others return -1.
+// (One thread stepping through the bins took 12 of a pass's 20 us.)
+__device__ __forceinline__ int rz_find(const uint32_t* h, int64_t rank, int64_t& before) {
+  const int lane = threadIdx.x & 63;
+  const uint4 b = *(const uint4*)(h + 4 * lane);
+  const int own = (int)(b.x + b.y + b.z + b.w);
+  int inc = own;
+#pragma unroll
+  for (int o = 1; o < 64; o <<= 1) {
+    const int y = __shfl_up(inc, o, 64);
+    if (lane >= o) inc += y;
+  }
+  const uint64_t over = __ballot((int64_t)inc > rank);
+  if (over == 0ull || lane != __builtin_ctzll(over)) return -1;
+  int cum = inc - own, k = 4 * lane;
+  const int bb[3] = {(int)b.x, (int)b.y, (int)b.z};
+  for (int q = 0; q < 3 && (int64_t)(cum + bb[q]) <= rank; ++q) { cum += bb[q]; ++k; }
+  before = cum;
+  return k;
+}
+
+// Counts the digit of each lane's key that matches the prefix; the values that
+// share the first lane's digit (most of them in the first passes) by one atomic.
+__device__ __forceinline__ void rz_count(uint32_t* h, uint32_t k, uint32_t prefix, int shift, int pass, bool valid) {
+  const bool on = valid && (pass == 0 || (k >> (shift + 8)) == (prefix >> (shift + 8)));
+  const uint32_t d = (k >> shift) & 255u;
+  const uint64_t m = __ballot(on);
+  if (m == 0ull) return;
+  const int lead = __builtin_ctzll(m);
+  const uint32_t dl = (uint32_t)__builtin_amdgcn_readlane((int)d, lead);
+  const uint64_t same = __ballot(on && d == dl);
+  if ((int)(threadIdx.x & 63) == lead) atomicAdd(&h[dl], (uint32_t)__popcll(same));
+  else if (on && d != dl) atomicAdd(&h[d], 1u);
+}
 
 __global__ void k_rz_init(Dims dm, RzState* R, int stage) {
   const int t = threadIdx.x;
@@ -297,7 +341,7 @@ __global__ void k_rz_init(Dims dm, RzState* R, int stage) {
 
 __global__ __launch_bounds__(256) void k_rz_hist(Dims dm, const float* __restrict__ kappa,
                                                  const float* __restrict__ surp, RzState* R, int stage, int pass) {
-  __shared__ uint32_t h[256];
+  __shared__ __align__(16) uint32_t h[256];
   __shared__ bool last;
   const int which = blockIdx.y;
   const float* src = which == 0 ? kappa : surp;
@@ -307,11 +351,15 @@ __global__ __launch_bounds__(256) void k_rz_hist(Dims dm, const float* __restric
   const int shift = 24 - 8 * pass;
   h[threadIdx.x] = 0;
   __syncthreads();
-  for (int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x; i < dm.T; i += (int64_t)gridDim.x * 256) {
-    const float v = absdev ? fabsf(src[i] - center) : src[i];
-    const uint32_t k = okey(v);
-    if (pass > 0 && (k >> (shift + 8)) != (prefix >> (shift + 8))) continue;
-    atomicAdd(&h[(k >> shift) & 255u], 1u);
+  constexpr int U = 4;
+  const int64_t stride = (int64_t)gridDim.x * 256;
+  for (int64_t i0 = (int64_t)blockIdx.x * 256 + threadIdx.x; i0 - threadIdx.x < dm.T; i0 += U * stride) {
+    float v[U];
+#pragma unroll
+    for (int u = 0; u < U; ++u) v[u] = i0 + u * stride < dm.T ? src[i0 + u * stride] : 0.f;
+#pragma unroll
+    for (int u = 0; u < U; ++u)
+      rz_count(h, okey(absdev ? fabsf(v[u] - center) : v[u]), prefix, shift, pass, i0 + u * stride < dm.T);
   }
   __syncthreads();
   if (h[threadIdx.x]) atomicAdd(&R->hist[which][threadIdx.x], h[threadIdx.x]);
@@ -321,23 +369,72 @@ __global__ __launch_bounds__(256) void k_rz_hist(Dims dm, const float* __restric
   __syncthreads();
   if (!last) return;
   // the last workgroup: the histogram in one coalesced device-coherent read,
-  // cleared for the next pass, then scanned by one thread
+  // cleared for the next pass, then scanned by one wave
   h[threadIdx.x] = ld_agent(&R->hist[which][threadIdx.x]);
   R->hist[which][threadIdx.x] = 0;
   __syncthreads();
-  if (threadIdx.x == 0) {
-    int64_t cum = 0, rank = R->rank[which];
-    for (int k = 0; k < 256; ++k) {
-      const int64_t hk = h[k];
-      if (cum + hk > rank) {
-        R->prefix[which] = prefix | ((uint32_t)k << shift);
-        R->rank[which] = rank - cum;
-        break;
-      }
-      cum += hk;
+  if (threadIdx.x < 64) {
+    int64_t before = 0;
+    const int k = rz_find(h, R->rank[which], before);
+    if (k >= 0) {
+      const uint32_t p = prefix | ((uint32_t)k << shift);
+      R->prefix[which] = p;
+      R->rank[which] -= before;
+      if (pass == 3) R->med[2 * stage + which] = okey_inv(p);
     }
-    R->done[which] = 0;
-    if (pass == 3) R->med[2 * stage + which] = okey_inv(R->prefix[which]);
+    if (threadIdx.x == 0) R->done[which] = 0;
+  }
+}
+
+// The same medians with one workgroup per select (kappa, s), both stages and all
+// passes in one launch, for sequences that one workgroup counts faster than eight
+// launches take: 18 us at 4 K values (160 us in launches), 297 us at 131 K (212 us).
+constexpr int64_t RZ_ONE = 32768;
+__global__ __launch_bounds__(1024) void k_rz_select(Dims dm, const float* __restrict__ kappa,
+                                                    const float* __restrict__ surp, RzState* R) {
+  __shared__ __align__(16) uint32_t h[256];
+  __shared__ uint32_t sprefix;
+  __shared__ int srank;
+  constexpr int U = 8;
+  const int which = blockIdx.x, tid = threadIdx.x, lane = tid & 63;
+  const float* src = which == 0 ? kappa : surp;
+  const int n = (int)dm.T;
+  float center = 0.f;
+  for (int stage = 0; stage < 2; ++stage) {
+    uint32_t prefix = 0;
+    int rank = (n - 1) / 2;
+    for (int pass = 0; pass < 4; ++pass) {
+      const int shift = 24 - 8 * pass;
+      if (tid < 256) h[tid] = 0;
+      __syncthreads();
+      for (int i0 = 0; i0 < n; i0 += U * 1024) {
+        float v[U];
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+          const int i = i0 + u * 1024 + tid;
+          v[u] = i < n ? src[i] : 0.f;
+        }
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+          rz_count(h, okey(stage == 1 ? fabsf(v[u] - center) : v[u]), prefix, shift, pass, i0 + u * 1024 + tid < n);
+        }
+      }
+      __syncthreads();
+      if (tid < 64) {
+        int64_t before = 0;
+        const int k = rz_find(h, rank, before);
+        if (k >= 0) {
+          sprefix = prefix | ((uint32_t)k << shift);
+          srank = rank - (int)before;
+        }
+      }
+      __syncthreads();
+      prefix = sprefix;
+      rank = srank;
+      __syncthreads();
+    }
+    center = okey_inv(prefix);
+    if (tid == 0) R->med[2 * stage + which] = center;
   }
 }
 
@@ -572,7 +669,7 @@ __global__ __launch_bounds__(256) void k_psum_apply(Dims dm, SegWs ws) {
 // the chunk-parallel form below give bit for bit the result of the serial
 // recurrence on the same integers, ties included:
 //   * the ends are cut into chunks of DPC; every chunk runs the recurrence from
-//     a guessed state DPM positions before it (all F there = 0), all chunks at
+//     a guessed state dp_margin positions before it (all F there = 0), all chunks at
 //     once;
 //   * if the guessed F over the 128 positions a chunk's ends can reach back to
 //     differ from the true F there by one constant, every F of the chunk
@@ -655,6 +752,23 @@ __device__ __forceinline__ long long dp_fix(double s, double sc) {
   return isfinite(s) ? (long long)__double2ll_rn(s * sc) : DP_NEG;
 }
 
+// Every score in fixed point, in place.  (Converted in the recurrence it was half
+// of each step's instructions: 163 us for the 2048 ends of a chunk and its
+// warm-up, 1.3 us a step.)
+__global__ __launch_bounds__(256) void k_dp_fixed(Dims dm, SegWs ws) {
+  const double sc = dp_scale(dm, ws);
+  const int64_t n2 = dm.N_c * (BAND / 2);
+  double2* S2 = (double2*)ws.S;
+  longlong2* F2 = (longlong2*)ws.S;
+  for (int64_t k = (int64_t)blockIdx.x * 256 + threadIdx.x; k < n2; k += (int64_t)gridDim.x * 256) {
+    const double2 v = S2[k];
+    longlong2 f;
+    f.x = dp_fix(v.x, sc);
+    f.y = dp_fix(v.y, sc);
+    F2[k] = f;
+  }
+}
+
 // one DPP step of the (value, smallest start) maximum within 16-lane rows
 // (an absent candidate is (DP_NEG, INT_MAX) and never wins)
 template <int CTRL>
@@ -682,19 +796,19 @@ __device__ __forceinline__ void dp_reduce16(long long& bv, int& ba) {
 // index position & 255) holds F of positions lo - 128 .. lo - 1 on entry.
 // Backpointer offsets go to Poff for ends >= own_lo; F of positions >= fg_lo
 // to Fg[position - fg_lo].
-__device__ void dp_run(const Dims& dm, const SegWs& ws, double sc, long long* Fr, int64_t lo, int64_t hi,
+__device__ void dp_run(const Dims& dm, const SegWs& ws, long long* Fr, int64_t lo, int64_t hi,
                        int64_t own_lo, long long* Fg, int64_t fg_lo) {
   const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
   const int st = lane >> 4, sub = lane & 15;
   // unconditional loads (row clamped to hi) keep the load counter exact
-  auto load = [&](int64_t i, double* sv) {
+  auto load = [&](int64_t i, long long* sv) {
     const int64_t ic = i <= hi ? i : hi;
-    const double2* p = (const double2*)(ws.S + (ic - 1) * BAND + sub * 8);
+    const longlong2* p = (const longlong2*)(ws.S + (ic - 1) * BAND + sub * 8);
 #pragma unroll
-    for (int k = 0; k < 4; ++k) { const double2 v = p[k]; sv[2 * k] = v.x; sv[2 * k + 1] = v.y; }
+    for (int k = 0; k < 4; ++k) { const longlong2 v = p[k]; sv[2 * k] = v.x; sv[2 * k + 1] = v.y; }
   };
   // scores of 4 steps in flight (static register indices: the step loop is unrolled by 4)
-  double sv[4][8];
+  long long sv[4][8];
 #pragma unroll
   for (int q = 0; q < 4; ++q) load(lo + 16 * q + 4 * wave + st, sv[q]);
   for (int64_t i00 = lo; i00 <= hi; i00 += 64) {
@@ -718,7 +832,7 @@ __device__ void dp_run(const Dims& dm, const SegWs& ws, double sc, long long* Fr
       int ba = 0x7fffffff;
 #pragma unroll
       for (int k = 0; k < 8; ++k) {
-        const long long s = dp_fix(sv[q][k], sc);
+        const long long s = sv[q][k];
         const bool ok = av[k] != 0x7fffffff && Fa[k] != DP_NEG && s != DP_NEG;
         const long long v = ok ? Fa[k] + s : DP_NEG;
         const int a = ok ? av[k] : 0x7fffffff;
@@ -740,16 +854,15 @@ __device__ void dp_run(const Dims& dm, const SegWs& ws, double sc, long long* Fr
 }
 
 // Guessed run of chunk c = blockIdx.x: ends c DPC + 1 .. min((c + 1) DPC, N),
-// warmed up from F = 0 at the 128 positions before max(c DPC - DPM, 0) (from
+// warmed up from F = 0 at the 128 positions before max(c DPC - margin, 0) (from
 // the true start F[0] = 0 when that is position 0).
 __global__ __launch_bounds__(256) void k_dp_chunk(Dims dm, SegWs ws) {
   __shared__ long long Fr[256];
   const int64_t N = dm.N_c;
   const int64_t c = blockIdx.x;
   const int64_t lo = c * DPC + 1, hi = (c + 1) * DPC < N ? (c + 1) * DPC : N;
-  const int64_t margin = dm.dp_serial ? 0 : DPM;
+  const int64_t margin = dm.dp_serial ? 0 : dp_margin(N);
   const int64_t s = c * DPC - margin > 0 ? c * DPC - margin : 0;
-  const double sc = dp_scale(dm, ws);
   long long* Fg = ws.Fg + c * (DPC + 128);
   const int64_t fg_lo = c * DPC - 127;
   // ring: positions s - 127 .. s (guess 0, or the true start)
@@ -764,7 +877,7 @@ __global__ __launch_bounds__(256) void k_dp_chunk(Dims dm, SegWs ws) {
     if (pos <= s) Fg[threadIdx.x] = pos < 0 ? DP_NEG : (s == 0 ? (pos == 0 ? 0 : DP_NEG) : 0);
   }
   __syncthreads();
-  dp_run(dm, ws, sc, Fr, s + 1, hi, lo, Fg, fg_lo);
+  dp_run(dm, ws, Fr, s + 1, hi, lo, Fg, fg_lo);
 }
 
 // For chunks c >= 1: is Fg[c-1] - Fg[c] one constant over positions
@@ -810,19 +923,28 @@ __global__ __launch_bounds__(256) void k_dp_fix(Dims dm, const float* __restrict
   int nfix = 0;
   if (tid == 0) ws.dlt[0] = 0;
   __shared__ long long tdiff[256];
-  __shared__ int tok[256];
+  __shared__ int firstbad;
   for (int64_t c = 1; c < C; ++c) {
-    if ((c - 1) % 256 == 0) {                  // stage the check results of the next 256 chunks
+    while (!dirty && c < C) {                  // up to 256 chunks at once, up to the first that fails its check
+      const int nb = (int)(C - c < 256 ? C - c : 256);
       __syncthreads();
-      if (c + tid < C) { tok[tid] = ws.cok[c + tid]; tdiff[tid] = ws.cdiff[c + tid]; }
+      if (tid == 0) firstbad = nb;
+      tdiff[tid] = tid < nb ? ws.cdiff[c + tid] : 0;
       __syncthreads();
+      if (tid < nb && !ws.cok[c + tid]) atomicMin(&firstbad, tid);
+      for (int o = 1; o < 256; o <<= 1) {      // inclusive scan of the offsets
+        const long long x = tid >= o ? tdiff[tid - o] : 0;
+        __syncthreads();
+        tdiff[tid] += x;
+        __syncthreads();
+      }
+      const int fb = firstbad;
+      if (tid < fb) ws.dlt[c + tid] = Dprev + tdiff[tid];
+      if (fb > 0) Dprev += tdiff[fb - 1];
+      c += fb;
+      if (fb < nb) break;
     }
-    const int tc = (int)((c - 1) % 256);
-    if (!dirty && tok[tc]) {
-      Dprev += tdiff[tc];
-      if (tid == 0) ws.dlt[c] = Dprev;
-      continue;
-    }
+    if (c >= C) break;
     // check against the true F of chunk c-1 (Fg + Dprev)
     long long dlo = LLONG_MAX, dhi = LLONG_MIN;
     int ng = 0;
@@ -856,7 +978,7 @@ __global__ __launch_bounds__(256) void k_dp_fix(Dims dm, const float* __restrict
     }
     __syncthreads();
     const int64_t lo = c * DPC + 1, hi = (c + 1) * DPC < N ? (c + 1) * DPC : N;
-    dp_run(dm, ws, sc, Fr, lo, hi, lo, Fg(c), c * DPC - 127);
+    dp_run(dm, ws, Fr, lo, hi, lo, Fg(c), c * DPC - 127);
     __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "workgroup");   // one workgroup: its global writes, visible to itself
     __syncthreads();
     Dprev = 0;
@@ -923,17 +1045,18 @@ __global__ void k_seg_empty(int32_t* slots, int32_t* nslots) {
 
 // ---- backtrack, chunk-parallel ---------------------------------------------
 // The path N = x_0 > x_1 > ... > x_J = 0 follows x_{m+1} = x_m - Poff[x_m]; the
-// slot starts are x_1 .. x_J.  A path node of chunk c (ends c DPC + 1 ..
-// (c + 1) DPC) is entered from the chunk above at one of its 128 top positions
+// slot starts are x_1 .. x_J.  A path node of chunk c (ends c BTC + 1 ..
+// (c + 1) BTC) is entered from the chunk above at one of its 128 top positions
 // (a slot is at most 128 long), so: every chunk walks from each of its 128
-// possible entries down to its exit (the first start <= c DPC, the entry of
+// possible entries down to its exit (the first start <= c BTC, the entry of
 // chunk c - 1), counting the starts it emits; one thread chains the entries
 // from N down; every chunk then re-walks from its true entry and writes its
 // starts at the offset the chain gives.
 __device__ __forceinline__ int bt_stage(const SegWs& ws, int64_t c, int64_t N, uint8_t* P) {
-  // P[k] = Poff[c DPC + 1 + k], k < DPC
-  const int64_t lo = c * DPC + 1;
-  const int n = (int)((c + 1) * DPC < N ? DPC : N - c * DPC);
+  // P[k] = Poff[c BTC + 1 + k], k < BTC
+  const int64_t lo = c * BTC + 1;
+  const int n = (int)((c + 1) * BTC < N ? BTC : N - c * BTC);
+#pragma unroll 16
   for (int k = threadIdx.x; k < n; k += blockDim.x) P[k] = ws.Poff[lo + k];
   __syncthreads();
   return n;
@@ -944,8 +1067,8 @@ __device__ __forceinline__ int bt_stage(const SegWs& ws, int64_t c, int64_t N, u
 __device__ __forceinline__ int2 bt_walk(int64_t c, const uint8_t* P, int64_t e) {
   int64_t p = e;
   int cnt = 0;
-  while (p > c * DPC) {
-    const int o = P[p - c * DPC - 1];
+  while (p > c * BTC) {
+    const int o = P[p - c * BTC - 1];
     if (o == 0) return make_int2(-1, cnt);
     p -= o;
     ++cnt;
@@ -953,30 +1076,30 @@ __device__ __forceinline__ int2 bt_walk(int64_t c, const uint8_t* P, int64_t e) 
   return make_int2((int)p, cnt);
 }
 
-// bt_tab[c * 128 + k] = (exit, count) of chunk c from entry (c + 1) DPC - 127 + k
+// bt_tab[c * 128 + k] = (exit, count) of chunk c from entry (c + 1) BTC - 127 + k
 // (the last chunk: entry N, k = 0)
 __global__ __launch_bounds__(128) void k_bt_walk(Dims dm, SegWs ws) {
-  __shared__ uint8_t P[DPC];
-  const int64_t N = dm.N_c, C = dp_chunks(N);
+  __shared__ uint8_t P[BTC];
+  const int64_t N = dm.N_c, C = bt_chunks(N);
   const int64_t c = blockIdx.x;
   bt_stage(ws, c, N, P);
   const int k = threadIdx.x;
-  int64_t e = (c + 1) * DPC - 127 + k;
+  int64_t e = (c + 1) * BTC - 127 + k;
   if (c == C - 1) {
     if (k != 0) return;
     e = N;
   }
-  ws.bt_tab[c * 128 + k] = e > c * DPC ? bt_walk(c, P, e) : make_int2(-1, 0);
+  ws.bt_tab[c * 128 + k] = e > c * BTC ? bt_walk(c, P, e) : make_int2(-1, 0);
 }
 
 // entries and output offsets of every chunk, J, slots[J] = N (one thread)
 __global__ void k_bt_chain(Dims dm, SegWs ws, int32_t* slots, int32_t* nslots) {
   if (threadIdx.x != 0) return;
-  const int64_t N = dm.N_c, C = dp_chunks(N);
+  const int64_t N = dm.N_c, C = bt_chunks(N);
   int64_t e = N;
   int total = 0;
   for (int64_t c = C - 1; c >= 0; --c) {
-    int k = c == C - 1 ? 0 : (int)(e - ((c + 1) * DPC - 127));
+    int k = c == C - 1 ? 0 : (int)(e - ((c + 1) * BTC - 127));
     if (e <= 0 || k < 0 || k >= 128) {       // the path ended (or broke) above this chunk
       ws.bt_ent[c] = make_int2(-1, 0);
       e = -1;
@@ -993,7 +1116,7 @@ __global__ void k_bt_chain(Dims dm, SegWs ws, int32_t* slots, int32_t* nslots) {
 
 // chunk c re-walks from its entry; the m-th start it emits is slots[J - 1 - (offset + m)]
 __global__ __launch_bounds__(64) void k_bt_emit(Dims dm, SegWs ws, int32_t* slots, const int32_t* nslots) {
-  __shared__ uint8_t P[DPC];
+  __shared__ uint8_t P[BTC];
   const int64_t N = dm.N_c;
   const int64_t c = blockIdx.x;
   const int2 ent = ws.bt_ent[c];
@@ -1003,8 +1126,8 @@ __global__ __launch_bounds__(64) void k_bt_emit(Dims dm, SegWs ws, int32_t* slot
   const int J = *nslots;
   int64_t p = ent.x;
   int m = ent.y;
-  while (p > c * DPC) {
-    const int o = P[p - c * DPC - 1];
+  while (p > c * BTC) {
+    const int o = P[p - c * BTC - 1];
     if (o == 0) break;
     p -= o;
     slots[J - 1 - m] = (int32_t)p;
@@ -1029,10 +1152,12 @@ hipError_t launch_segment(const Dims& dm, const void* hidden, const float* surpr
   hipLaunchKernelGGL(k_stabilize, dim3((unsigned)((dm.T + 255) / 256)), dim3(256), 0, st, dm, ws, kappa);
   {
     RzState* R = (RzState*)ws.rz;
-    for (int stage = 0; stage < 2; ++stage) {
+    if (dm.T <= RZ_ONE) {
+      hipLaunchKernelGGL(k_rz_select, dim3(2), dim3(1024), 0, st, dm, (const float*)kappa, surprisal, R);
+    } else for (int stage = 0; stage < 2; ++stage) {
       hipLaunchKernelGGL(k_rz_init, dim3(1), dim3(256), 0, st, dm, R, stage);
       for (int pass = 0; pass < 4; ++pass)
-        hipLaunchKernelGGL(k_rz_hist, dim3(RZ_WG, 2), dim3(256), 0, st, dm, (const float*)kappa, surprisal, R, stage,
+        hipLaunchKernelGGL(k_rz_hist, dim3(rz_workgroups(dm.T), 2), dim3(256), 0, st, dm, (const float*)kappa, surprisal, R, stage,
                            pass);
     }
     hipLaunchKernelGGL(k_rz_score, dim3((unsigned)((dm.T + 255) / 256)), dim3(256), 0, st, dm, (const float*)kappa,
@@ -1054,12 +1179,15 @@ hipError_t launch_segment(const Dims& dm, const void* hidden, const float* surpr
     const int64_t C = dp_chunks(dm.N_c);
     hipLaunchKernelGGL(k_slot_scores, dim3((unsigned)((dm.N_c + SLE - 1) / SLE)), dim3(BAND), 0, st, dm,
                        (const float*)bscore, ws);
+    // a thread converts four pairs at least; every workgroup reduces the N_c / 16 maxima
+    hipLaunchKernelGGL(k_dp_fixed, dim3((unsigned)std::min<int64_t>((dm.N_c * (BAND / 2) + 1023) / 1024, 1024)), dim3(256), 0,
+                       st, dm, ws);
     hipLaunchKernelGGL(k_dp_chunk, dim3((unsigned)C), dim3(256), 0, st, dm, ws);
     if (C > 1) hipLaunchKernelGGL(k_dp_check, dim3((unsigned)(C - 1)), dim3(128), 0, st, dm, ws);
     hipLaunchKernelGGL(k_dp_fix, dim3(1), dim3(256), 0, st, dm, (const float*)bscore, ws);
-    hipLaunchKernelGGL(k_bt_walk, dim3((unsigned)C), dim3(128), 0, st, dm, ws);
+    hipLaunchKernelGGL(k_bt_walk, dim3((unsigned)bt_chunks(dm.N_c)), dim3(128), 0, st, dm, ws);
     hipLaunchKernelGGL(k_bt_chain, dim3(1), dim3(64), 0, st, dm, ws, slot_starts, n_slots);
-    hipLaunchKernelGGL(k_bt_emit, dim3((unsigned)C), dim3(64), 0, st, dm, ws, slot_starts, (const int32_t*)n_slots);
+    hipLaunchKernelGGL(k_bt_emit, dim3((unsigned)bt_chunks(dm.N_c)), dim3(64), 0, st, dm, ws, slot_starts, (const int32_t*)n_slots);
   } else {
     hipLaunchKernelGGL(k_seg_empty, dim3(1), dim3(64), 0, st, slot_starts, n_slots);
   }
