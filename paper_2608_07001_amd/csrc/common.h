@@ -193,20 +193,23 @@ __device__ __forceinline__ int round_half_even_mid(int x0, int x1) {
 constexpr int32_t STATUS_NUMERIC = 1, STATUS_PARTITION = 2, STATUS_CAPACITY = 4;
 constexpr int32_t STATUS_BUILT = 0x4b56424c;
 
-// a node to refine, appended to its list: one of the long classes, or the subtrees of (l, g)
+// The lists of nodes to refine: 0, 1, 2 the long classes, 3 + lg the subtrees of (l, g).
+__device__ __forceinline__ int list_of(int n, int lg) {
+  return n > NMAX / 2 ? 0 : (n > NMAX / 4 ? 1 : (n > ST_N ? 2 : 3 + lg));
+}
+__device__ __forceinline__ int32_t* list_counter(const TreeView& tv, int list) {
+  return list < 3 ? tv.lv_ctr + list : tv.sub_ctr + (list - 3);
+}
+// place `pos` of a list; null past its end (never: the nodes of a list are disjoint)
+__device__ __forceinline__ int32_t* list_item(const TreeView& tv, int list, int64_t scap, int pos) {
+  if (list >= 3) return pos < scap ? tv.sub_items + 8 * ((list - 3) * scap + pos) : nullptr;
+  int32_t* l = list == 0 ? tv.long_items[0] : (list == 1 ? tv.long_items[1] : tv.long_items[2]);
+  return pos < tv.long_cap ? l + 8 * (int64_t)pos : nullptr;
+}
+// one node appended to its list (d0.z: length in the low byte)
 __device__ __forceinline__ void push_node(const TreeView& tv, const Dims& dm, int lg, int4 d0, int4 d1) {
-  int32_t* dst = nullptr;
-  const int n = d0.z & 255;
-  if (n <= ST_N) {
-    const int pos = atomicAdd(&tv.sub_ctr[lg], 1);
-    const int64_t cap = short_capacity(dm.N_c);
-    if (pos < cap) dst = tv.sub_items + 8 * ((int64_t)lg * cap + pos);
-  } else {
-    const int c = n > NMAX / 2 ? 0 : (n > NMAX / 4 ? 1 : 2);
-    const int pos = atomicAdd(&tv.lv_ctr[c], 1);
-    if (pos < tv.long_cap) dst = (c == 0 ? tv.long_items[0] : (c == 1 ? tv.long_items[1] : tv.long_items[2])) + 8 * (int64_t)pos;
-  }
-  // never: the nodes of a list are disjoint
+  const int list = list_of(d0.z & 255, lg);
+  int32_t* dst = list_item(tv, list, short_capacity(dm.N_c), atomicAdd(list_counter(tv, list), 1));
   if (!dst) { atomicOr(tv.status, STATUS_CAPACITY); return; }
   ((int4*)dst)[0] = d0;
   ((int4*)dst)[1] = d1;

@@ -36,17 +36,34 @@ __device__ __forceinline__ bool on_frontier(const TreeView& tv, int64_t u, int64
   return tv.node_nch[base + i] == 0 || tv.sp_exec[base + i] == 0;
 }
 
-__global__ void k_pack_count(Dims dm, TreeView tv, PackWs pw) {
-  const int64_t u = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (u >= (int64_t)dm.L * dm.G * dm.J_cap) return;
-  const int lg = (int)(u / dm.J_cap), j = (int)(u % dm.J_cap);
+// a wave counts PC_U units, one after the other (nodes across the lanes: one
+// thread per unit read a cache line for every node)
+constexpr int PC_U = 8;
+__global__ __launch_bounds__(256) void k_pack_count(Dims dm, TreeView tv, PackWs pw) {
+  const int wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6), lane = threadIdx.x & 63;
+  const int64_t units = (int64_t)dm.L * dm.G * dm.J_cap;
+  const int64_t u0 = ((int64_t)blockIdx.x * 4 + wave) * PC_U;
   const int J = *tv.nslots;
-  if (j >= J) { pw.ucount[u] = 0; return; }
-  const int64_t base = (int64_t)lg * 2 * dm.N_c + 2 * (int64_t)tv.slots[j];
-  const int nn = tv.unit_nn[u];
-  int c = 0;
-  for (int i = 0; i < nn; ++i) c += on_frontier(tv, u, base, i);
-  pw.ucount[u] = c;
+  // a unit whose Add was not executed has nothing on its frontier, one that is a lone root has it
+  int nn = 0, c = 0;
+  const int64_t u = u0 + lane;
+  const bool mine = lane < PC_U && u < units;
+  if (mine && (int)(u % dm.J_cap) < J && tv.add_exec[u] != 0) {
+    nn = tv.unit_nn[u];
+    c = nn == 1 ? 1 : 0;
+  }
+  uint64_t more = __ballot(nn > 1);
+  while (more != 0ull) {
+    const int q = __builtin_ctzll(more);
+    more &= more - 1;
+    const int n = __builtin_amdgcn_readlane(nn, q);
+    const int64_t uq = u0 + q;
+    const int64_t base = (uq / dm.J_cap) * 2 * dm.N_c + 2 * (int64_t)tv.slots[uq % dm.J_cap];
+    int k = 0;
+    for (int i0 = 0; i0 < n; i0 += 64) k += __popcll(__ballot(i0 + lane < n && on_frontier(tv, uq, base, i0 + lane)));
+    if (lane == q) c = k;
+  }
+  if (mine) pw.ucount[u] = c;
 }
 
 // per (l, g): exclusive scan over its units, then the (l, g) entry count
@@ -102,41 +119,57 @@ __global__ __launch_bounds__(64) void k_pack_emit(Dims dm, const T* __restrict__
   const int lane = threadIdx.x;
   const int64_t base = (int64_t)lg * 2 * dm.N_c + 2 * (int64_t)tv.slots[j];
   const int nn = tv.unit_nn[u];
-  __shared__ int fa[NODE_MAX];
-  __shared__ int fid[NODE_MAX];
-  __shared__ int nf;
+  const int cnt = pw.ucount[u];
+  if (cnt < 1) return;
+  __shared__ uint32_t mask[NMAX / 32];      // starts of the frontier nodes, relative to the slot's
+  __shared__ int at[NMAX];                  // by start: node index | length << 16
+  __shared__ int list[NMAX];                // by rank: start | length << 8 | (the root) << 16
   __shared__ float mk[D];
-  if (lane == 0) nf = 0;
+  if (lane < NMAX / 32) mask[lane] = 0u;
   __syncthreads();
-  // frontier nodes; their rank by start gives the output order
-  for (int i = lane; i < nn; i += 64) fa[i] = on_frontier(tv, u, base, i) ? tv.node_a[base + i] : -1;
+  // the output order is that of the starts: ranks are population counts
+  const int s0 = tv.slots[j];
+  for (int i = lane; i < nn; i += 64)
+    if (on_frontier(tv, u, base, i)) {
+      const int a = (tv.node_a[base + i] - s0) & (NMAX - 1);
+      atomicOr(&mask[a >> 5], 1u << (a & 31));
+      at[a] = i | (tv.node_n[base + i] << 16);
+    }
   __syncthreads();
-  for (int i = lane; i < nn; i += 64) {
-    if (fa[i] < 0) continue;
-    int rank = 0;
-    for (int k = 0; k < nn; ++k) rank += (fa[k] >= 0 && fa[k] < fa[i]);
-    fid[rank] = i;
+#pragma unroll
+  for (int h = 0; h < NMAX / 64; ++h) {
+    const int a = lane + 64 * h;
+    if ((mask[a >> 5] >> (a & 31)) & 1u) {
+      int rank = __popc(mask[a >> 5] & ((1u << (a & 31)) - 1u));
+      for (int k = 0; k < (a >> 5); ++k) rank += __popc(mask[k]);
+      list[rank] = a | ((at[a] >> 16) << 8) | ((at[a] & 0xffff) == 0 ? 1 << 16 : 0);
+    }
   }
   __syncthreads();
-  const int cnt = pw.ucount[u];
   const int64_t out0 = offsets[lg] + pw.uoff[u];
   const T* Kp = K + (int64_t)lg * dm.T * D;
   const T* Vp = V + (int64_t)lg * dm.T * D;
   const float* Rt = tv.tok_R + (int64_t)lg * dm.N_c;
-  for (int r = 0; r < cnt; ++r) {
-    const int i = fid[r];
-    const int a = tv.node_a[base + i], n = tv.node_n[base + i];
+  // singletons: the original rows, 16 bytes a lane, several entries at a time
+  constexpr int LPR = D * (int)sizeof(T) / 16, EPS = 64 / LPR;
+  for (int r0 = 0; r0 < cnt; r0 += EPS) {
+    const int r = r0 + lane / LPR, c = lane % LPR;
+    const int it = r < cnt ? list[r] : 0;
+    if (((it >> 8) & 255) != 1) continue;
     const int64_t o = out0 + r;
+    if (o >= dm.B_total) { atomicOr(tv.status, STATUS_CAPACITY); continue; }
+    const int a = s0 + (it & 255);
+    ((uint4*)(Ko + o * D))[c] = ((const uint4*)(Kp + (int64_t)a * D))[c];
+    ((uint4*)(Vo + o * D))[c] = ((const uint4*)(Vp + (int64_t)a * D))[c];
+    if (c == 0) { po[o] = a; lo[o] = 0.f; }
+  }
+  for (int r = 0; r < cnt; ++r) {
+    const int it = __builtin_amdgcn_readfirstlane(list[r]);
+    const int a = s0 + (it & 255), n = (it >> 8) & 255;
+    const int64_t o = out0 + r;
+    if (n == 1) continue;
     if (o >= dm.B_total) { if (lane == 0) atomicOr(tv.status, STATUS_CAPACITY); break; }
-    if (n == 1) {
-      for (int c = lane; c < D; c += 64) {
-        Ko[o * D + c] = Kp[(int64_t)a * D + c];
-        Vo[o * D + c] = Vp[(int64_t)a * D + c];
-      }
-      if (lane == 0) { po[o] = a; lo[o] = 0.f; }
-      continue;
-    }
-    if (i == 0) {                             // the root: the prototype the build stored
+    if (it >> 16) {                           // the root: the prototype the build stored
       const T* pr = (const T*)tv.proto + u * 2 * D;
       for (int c = lane; c < D; c += 64) {
         Ko[o * D + c] = pr[c];
@@ -149,28 +182,48 @@ __global__ __launch_bounds__(64) void k_pack_emit(Dims dm, const T* __restrict__
 #pragma unroll
     for (int k = 0; k < DL; ++k) { sk[k] = 0.f; srv[k] = 0.f; sv[k] = 0.f; }
     float sr = 0.f, skn = 0.f;
-    for (int t = a; t < a + n; ++t) {
-      const float rt = Rt[t];
-      float kk = 0.f;
+    constexpr int TU = 4;                     // tokens in flight
+    for (int t0 = a; t0 < a + n; t0 += TU) {
+      float x[TU][DL], y[TU][DL], v[TU][DL], c[TU][DL], s[TU][DL], rt[TU], kk[TU];
 #pragma unroll
-      for (int k = 0; k < DL; ++k) {
-        const int i2 = lane + 64 * k;
-        if (i2 < D) {
+      for (int q = 0; q < TU; ++q) {
+        const int t = t0 + q < a + n ? t0 + q : a + n - 1;
+        rt[q] = Rt[t];
+#pragma unroll
+        for (int k = 0; k < DL; ++k) {
+          const int i2 = lane + 64 * k < D ? lane + 64 * k : 0;
           const int ih = i2 < H2 ? i2 : i2 - H2;
           const int ip = i2 < H2 ? i2 + H2 : i2 - H2;
-          const float c = cosT[(int64_t)t * H2 + ih], s = sinT[(int64_t)t * H2 + ih];
-          const float x = ldf(Kp, (int64_t)t * D + i2), y = ldf(Kp, (int64_t)t * D + ip);
-          const float kr = i2 < H2 ? x * c + y * s : x * c - y * s;
-          const float v = ldf(Vp, (int64_t)t * D + i2);
-          sk[k] += kr;
-          srv[k] += rt * v;
-          sv[k] += v;
-          kk += x * x;
+          c[q][k] = cosT[(int64_t)t * H2 + ih];
+          s[q][k] = sinT[(int64_t)t * H2 + ih];
+          x[q][k] = ldf(Kp, (int64_t)t * D + i2);
+          y[q][k] = ldf(Kp, (int64_t)t * D + ip);
+          v[q][k] = ldf(Vp, (int64_t)t * D + i2);
         }
       }
-      kk = wave_sum(kk);
-      skn += sqrtf(kk);
-      sr += rt;
+#pragma unroll
+      for (int q = 0; q < TU; ++q) {
+        kk[q] = 0.f;
+#pragma unroll
+        for (int k = 0; k < DL; ++k)
+          if (lane + 64 * k < D) kk[q] += x[q][k] * x[q][k];
+        kk[q] = wave_sum_dpp(kk[q]);
+      }
+#pragma unroll
+      for (int q = 0; q < TU; ++q) {
+        if (t0 + q >= a + n) break;
+#pragma unroll
+        for (int k = 0; k < DL; ++k) {
+          const int i2 = lane + 64 * k;
+          if (i2 < D) {
+            sk[k] += i2 < H2 ? x[q][k] * c[q][k] + y[q][k] * s[q][k] : x[q][k] * c[q][k] - y[q][k] * s[q][k];
+            srv[k] += rt[q] * v[q][k];
+            sv[k] += v[q][k];
+          }
+        }
+        skn += sqrtf(kk[q]);
+        sr += rt[q];
+      }
     }
     const float inv = 1.0f / (float)n;
     float ss = 0.f;
@@ -179,7 +232,7 @@ __global__ __launch_bounds__(64) void k_pack_emit(Dims dm, const T* __restrict__
       const int i2 = lane + 64 * k;
       if (i2 < D) { mk[i2] = sk[k] * inv; ss += mk[i2] * mk[i2]; }
     }
-    ss = wave_sum(ss);
+    ss = wave_sum_dpp(ss);
     __syncthreads();
     const float coh = sqrtf(ss) / (skn * inv + dm.eps);
     const float me = fminf(fmaxf((float)n * coh * coh, 1.0f), (float)n);
@@ -225,7 +278,7 @@ hipError_t launch_pack(const Dims& dm, const void* K, const void* V, const float
   PackWs pw = pack_view(ws, dm);
   const int64_t units = (int64_t)dm.L * dm.G * dm.J_cap;
   const int LG = dm.L * dm.G;
-  hipLaunchKernelGGL(k_pack_count, dim3((unsigned)((units + 127) / 128)), dim3(128), 0, st, dm, tv, pw);
+  hipLaunchKernelGGL(k_pack_count, dim3((unsigned)((units + 4 * PC_U - 1) / (4 * PC_U))), dim3(256), 0, st, dm, tv, pw);
   hipLaunchKernelGGL(k_pack_scan_units, dim3(LG), dim3(256), 0, st, dm, tv, pw, counts);
   hipLaunchKernelGGL(k_pack_scan_lg, dim3(1), dim3(64), 0, st, dm, (const int64_t*)counts, offsets);
   const int clk = clock_begin(dm, GRACEKV_STAGE_PACK, st);

@@ -49,7 +49,8 @@ __global__ void k_sub_reset(const Dims* __restrict__ dmp, const TreeView* __rest
   for (int i = threadIdx.x; i < LG; i += blockDim.x) tv.sub_ctr[i] = 0;
 }
 
-// The children of every refined root, one unit per thread.
+// The children of every refined root, one unit per thread; the lanes of a wave
+// that list into the same place take one block of it.
 __global__ __launch_bounds__(256) void k_sub_first(const Dims* __restrict__ dmp, const TreeView* __restrict__ tvp,
                                                    int full) {
   const Dims& dm = *dmp;
@@ -57,22 +58,47 @@ __global__ __launch_bounds__(256) void k_sub_first(const Dims* __restrict__ dmp,
   const int nunits = tv.wctr[8];
   const int J = *tv.nslots;
   const uint64_t theta = full ? 0ull : tv.theta[0];
-  for (int k = (int)(blockIdx.x * blockDim.x + threadIdx.x); k < nunits; k += (int)(gridDim.x * blockDim.x)) {
-    const int unit = tv.work[8 * (int64_t)k];
-    const int lg = unit / dm.J_cap, j = unit % dm.J_cap;
-    if (j >= J) continue;
-    const int64_t base = (int64_t)lg * 2 * dm.N_c + 2 * (int64_t)tv.slots[j];
-    const int cnt = tv.unit_nn[unit];
-    if (cnt < 2 || cnt > 4) continue;
-    const uint64_t Ef = full ? ~0ull : tv.sp_E[base];        // the root's Split
-    if (Ef < theta) continue;
-    const float w = tv.omega[lg];
-    for (int c = 1; c < cnt; ++c) {
-      const int n = tv.node_n[base + c];
-      if (n < 2) continue;
-      push_node(tv, dm, lg, make_int4(unit, tv.node_a[base + c], n | (1 << 8) | (c << 16),
-                                         __float_as_int(tv.node_D[base + c])),
-                make_int4(__float_as_int(tv.node_R[base + c]), __float_as_int(w), (int32_t)(Ef >> 32), 0));
+  const int lane = threadIdx.x & 63;
+  const int64_t scap = short_capacity(dm.N_c);
+  for (int k0 = (int)(blockIdx.x * blockDim.x + (threadIdx.x & ~63u)); k0 < nunits; k0 += (int)(gridDim.x * blockDim.x)) {
+    const int k = k0 + lane;
+    int unit = 0, lg = 0, cnt = 0;
+    int64_t base = 0;
+    uint64_t Ef = 0ull;
+    if (k < nunits) {
+      unit = tv.work[8 * (int64_t)k];
+      lg = unit / dm.J_cap;
+      const int j = unit % dm.J_cap;
+      if (j < J) {
+        base = (int64_t)lg * 2 * dm.N_c + 2 * (int64_t)tv.slots[j];
+        cnt = tv.unit_nn[unit];
+        Ef = full ? ~0ull : tv.sp_E[base];                   // the root's Split
+        if (cnt < 2 || cnt > 4 || Ef < theta) cnt = 0;
+      }
+    }
+    const float w = cnt ? tv.omega[lg] : 0.f;
+    for (int c = 1; c < 4; ++c) {
+      const int n = c < cnt ? tv.node_n[base + c] : 0;
+      const int dest = n < 2 ? -1 : list_of(n, lg);
+      uint64_t todo = __ballot(dest >= 0);
+      while (todo != 0ull) {
+        const int lead = __builtin_ctzll(todo);
+        const int d = __builtin_amdgcn_readlane(dest, lead);
+        const uint64_t same = __ballot(dest == d);
+        todo &= ~same;
+        int first = 0;
+        if (lane == lead) first = atomicAdd(list_counter(tv, d), __popcll(same));
+        first = __builtin_amdgcn_readlane(first, lead);
+        if (dest == d) {
+          int32_t* dst = list_item(tv, d, scap, first + __popcll(same & ((1ull << lane) - 1ull)));
+          if (dst) {
+            ((int4*)dst)[0] = make_int4(unit, tv.node_a[base + c], n | (1 << 8) | (c << 16), __float_as_int(tv.node_D[base + c]));
+            ((int4*)dst)[1] = make_int4(__float_as_int(tv.node_R[base + c]), __float_as_int(w), (int32_t)(Ef >> 32), 0);
+          } else {
+            atomicOr(tv.status, STATUS_CAPACITY);
+          }
+        }
+      }
     }
   }
 }
