@@ -10,8 +10,8 @@
 // and value are read once for all query heads of its group.
 //   * grid (P, L*G), 256 threads: workgroup p of (l, g) takes the p-th of P
 //     contiguous ranges of the row.  One entry sits on D/8 lanes (eight dims
-//     each), so a wave reads whole rows, the next entry's rows in flight while
-//     the current one is folded in; each such lane group keeps a base-2
+//     each), so a wave reads whole rows, the next entries' rows in flight
+//     while the current ones are folded in; each such lane group keeps a base-2
 //     online-softmax state per query head (running max, sum, its eight output
 //     dims).  The lane groups of a wave merge through row-swap permutations,
 //     the four waves through LDS; the partial state goes to the workspace.
@@ -112,6 +112,15 @@ __device__ __forceinline__ float group_sum(float v) {
   return col_sum4(v);
 }
 
+// Entries that a lane group folds in at once.  More share one maximum and one
+// rescaling, but their rows and products take registers that waves in flight need:
+// measured (us, one against this many) 16.5 -> 14.2 for one head (8.4 MB of rows
+// a layer group, 4), 27.0 -> 25.5 for four heads of 64 (2), 14.3 -> 13.6 in fp32
+// (2); four heads of 128 lose (39.3 -> 41.1 with 2) and eight of them do not fit.
+__host__ __device__ constexpr int dec_block(bool bf16, int d, int hpg) {
+  return hpg == 8 || (d == 128 && hpg == 4) ? 1 : (hpg == 1 && bf16 ? 4 : 2);
+}
+
 template <typename T, int D, int HPG>
 __global__ __launch_bounds__(DEC_T) void k_decode(Dims dm, int P, const T* __restrict__ q,
                                                   const int64_t* __restrict__ offsets, const T* __restrict__ Kout,
@@ -120,6 +129,7 @@ __global__ __launch_bounds__(DEC_T) void k_decode(Dims dm, int P, const T* __res
                                                   float2* __restrict__ pml, float* __restrict__ po) {
   constexpr int LPE = D / 8;                  // lanes per entry
   constexpr int EPW = 64 / LPE;               // entries per wave step
+  constexpr int EB = dec_block(sizeof(T) == 2, D, HPG);   // entries per lane group at a time
   constexpr float LOG2E = 1.44269504088896341f;
   __shared__ float sM[DEC_W][HPG], sS[DEC_W][HPG];
   __shared__ float sO[DEC_W][HPG][D];
@@ -142,10 +152,13 @@ __global__ __launch_bounds__(DEC_T) void k_decode(Dims dm, int P, const T* __res
 #pragma unroll
     for (int j = 0; j < 8; ++j) qv[h][j] *= sc2;
   }
+  // below every logit, finite: a state that has seen nothing, or only an absent
+  // entry (logit -inf), stays (NONE, 0, 0) without a test
+  constexpr float NONE = -3.0e38f;
   float m[HPG], s[HPG], o[HPG][8];
 #pragma unroll
   for (int h = 0; h < HPG; ++h) {
-    m[h] = -INFINITY;
+    m[h] = NONE;
     s[h] = 0.f;
 #pragma unroll
     for (int j = 0; j < 8; ++j) o[h][j] = 0.f;
@@ -163,45 +176,58 @@ __global__ __launch_bounds__(DEC_T) void k_decode(Dims dm, int P, const T* __res
       lm = 0.f;
     }
   };
-  // wave-uniform trip count; a lane group past e1 contributes nothing
-  constexpr int64_t STEP = (int64_t)DEC_W * EPW;
-  Raw8<T> kn, vn;
-  float lmn = 0.f;
-  {
-    const int64_t e = e0 + (int64_t)w * EPW + row;
-    const T* kr;
-    const T* vr;
-    locate(e < e1 ? e : e0, kr, vr, lmn);
-    if (e0 < e1) { kn.load(kr + 8 * sub); vn.load(vr + 8 * sub); }
-  }
-  for (int64_t eb = e0 + (int64_t)w * EPW; eb < e1; eb += STEP) {
-    const bool on = eb + row < e1;
-    float kx[8], vx[8];
-    kn.get(kx);
-    vn.get(vx);
-    const float lm = lmn;
-    if (eb + STEP < e1) {                     // the next entry of this lane group, in flight
-      const int64_t e = eb + STEP + row;
+  // EB entries per lane group at a time, the next ones in flight: one maximum and
+  // one rescaling of the running state for all of them.  Wave-uniform trip count;
+  // an entry past e1 contributes nothing.
+  constexpr int64_t STEP = (int64_t)DEC_W * EPW * EB;
+  Raw8<T> kn[EB], vn[EB];
+  float lmn[EB];
+  auto fetch = [&](int64_t eb) {
+#pragma unroll
+    for (int b = 0; b < EB; ++b) {
+      const int64_t e = eb + b * EPW + row;
       const T* kr;
       const T* vr;
-      locate(e < e1 ? e : e0, kr, vr, lmn);
-      kn.load(kr + 8 * sub);
-      vn.load(vr + 8 * sub);
+      locate(e < e1 ? e : e0, kr, vr, lmn[b]);
+      if (e >= e1) lmn[b] = -INFINITY;
+      kn[b].load(kr + 8 * sub);
+      vn[b].load(vr + 8 * sub);
     }
+  };
+  const int64_t w0 = e0 + (int64_t)w * EPW * EB;
+  if (w0 < e1) fetch(w0);
+  for (int64_t eb = w0; eb < e1; eb += STEP) {
+    float kx[EB][8], vx[EB][8], lm[EB];
+#pragma unroll
+    for (int b = 0; b < EB; ++b) {
+      kn[b].get(kx[b]);
+      vn[b].get(vx[b]);
+      lm[b] = lmn[b];
+    }
+    if (eb + STEP < e1) fetch(eb + STEP);
 #pragma unroll
     for (int h = 0; h < HPG; ++h) {
-      float x = 0.f;
+      float x[EB];
+      float mn = m[h];
 #pragma unroll
-      for (int j = 0; j < 8; ++j) x += qv[h][j] * kx[j];
-      x = entry_sum<D>(x) + lm;
-      if (on) {
-        const float mn = fmaxf(m[h], x);
-        const float c = __builtin_amdgcn_exp2f(m[h] - mn);
-        const float pe = __builtin_amdgcn_exp2f(x - mn);
-        s[h] = s[h] * c + pe;
+      for (int b = 0; b < EB; ++b) {
+        float t = 0.f;
 #pragma unroll
-        for (int j = 0; j < 8; ++j) o[h][j] = o[h][j] * c + pe * vx[j];
-        m[h] = mn;
+        for (int j = 0; j < 8; ++j) t += qv[h][j] * kx[b][j];
+        x[b] = entry_sum<D>(t) + lm[b];
+        mn = fmaxf(mn, x[b]);
+      }
+      const float c = __builtin_amdgcn_exp2f(m[h] - mn);
+      m[h] = mn;
+      s[h] *= c;
+#pragma unroll
+      for (int j = 0; j < 8; ++j) o[h][j] *= c;
+#pragma unroll
+      for (int b = 0; b < EB; ++b) {
+        const float pe = __builtin_amdgcn_exp2f(x[b] - mn);
+        s[h] += pe;
+#pragma unroll
+        for (int j = 0; j < 8; ++j) o[h][j] += pe * vx[b][j];
       }
     }
   }
