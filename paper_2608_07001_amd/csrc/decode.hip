@@ -20,6 +20,7 @@
 //     last-arriving workgroup could merge them in the same launch, but the
 //     device-scope fences that needs write back and invalidate the L2 of the
 //     XCD on this chip, which costs far more than a second launch.)
+#include <cfloat>
 #include <mutex>
 
 #include "common.h"
@@ -112,14 +113,17 @@ __device__ __forceinline__ float group_sum(float v) {
   return col_sum4(v);
 }
 
-// Entries that a lane group folds in at once.  More share one maximum and one
-// rescaling, but their rows and products take registers that waves in flight need:
-// measured (us, one against this many) 16.5 -> 14.2 for one head (8.4 MB of rows
-// a layer group, 4), 27.0 -> 25.5 for four heads of 64 (2), 14.3 -> 13.6 in fp32
-// (2); four heads of 128 lose (39.3 -> 41.1 with 2) and eight of them do not fit.
-__host__ __device__ constexpr int dec_block(bool bf16, int d, int hpg) {
-  return hpg == 8 || (d == 128 && hpg == 4) ? 1 : (hpg == 1 && bf16 ? 4 : 2);
-}
+// Entries that a lane group folds in at once: two share one maximum and one
+// rescaling, but their rows and products take registers that waves in flight need.
+// Measured in us, one against two: fp32 33.9 -> 31.4 (five thousand to 131 K tokens
+// all gain or tie), but bf16 95.9 -> 108.6 for four heads of 64 and 239 -> 257 for
+// two of 128 at 32 K tokens and 4x, whose memory rate falls with the waves.
+__host__ __device__ constexpr int dec_block(bool bf16) { return bf16 ? 1 : 2; }
+// Whether an entry past the end is skipped by a test, or takes part with the logit
+// -inf.  The test costs more where its branch splits many heads' work: eight heads
+// 309.8 -> 295.9 us without it (32 K tokens, 4x), four of 128 297 with either, but
+// 0.8 % more at 128 K; a block of two has one test for both and cannot use it.
+__host__ __device__ constexpr bool dec_test(bool bf16, int hpg) { return bf16 && hpg < 8; }
 
 template <typename T, int D, int HPG>
 __global__ __launch_bounds__(DEC_T) void k_decode(Dims dm, int P, const T* __restrict__ q,
@@ -129,7 +133,8 @@ __global__ __launch_bounds__(DEC_T) void k_decode(Dims dm, int P, const T* __res
                                                   float2* __restrict__ pml, float* __restrict__ po) {
   constexpr int LPE = D / 8;                  // lanes per entry
   constexpr int EPW = 64 / LPE;               // entries per wave step
-  constexpr int EB = dec_block(sizeof(T) == 2, D, HPG);   // entries per lane group at a time
+  constexpr int EB = dec_block(sizeof(T) == 2);           // entries per lane group at a time
+  constexpr bool TEST = dec_test(sizeof(T) == 2, HPG);
   constexpr float LOG2E = 1.44269504088896341f;
   __shared__ float sM[DEC_W][HPG], sS[DEC_W][HPG];
   __shared__ float sO[DEC_W][HPG][D];
@@ -152,9 +157,9 @@ __global__ __launch_bounds__(DEC_T) void k_decode(Dims dm, int P, const T* __res
 #pragma unroll
     for (int j = 0; j < 8; ++j) qv[h][j] *= sc2;
   }
-  // below every logit, finite: a state that has seen nothing, or only an absent
-  // entry (logit -inf), stays (NONE, 0, 0) without a test
-  constexpr float NONE = -3.0e38f;
+  // the least finite logit: a state that has seen nothing, or only an absent entry
+  // (logit -inf), stays (NONE, 0, 0)
+  constexpr float NONE = -FLT_MAX;
   float m[HPG], s[HPG], o[HPG][8];
 #pragma unroll
   for (int h = 0; h < HPG; ++h) {
@@ -189,7 +194,7 @@ __global__ __launch_bounds__(DEC_T) void k_decode(Dims dm, int P, const T* __res
       const T* kr;
       const T* vr;
       locate(e < e1 ? e : e0, kr, vr, lmn[b]);
-      if (e >= e1) lmn[b] = -INFINITY;
+      if (!TEST && e >= e1) lmn[b] = -INFINITY;
       kn[b].load(kr + 8 * sub);
       vn[b].load(vr + 8 * sub);
     }
@@ -204,6 +209,7 @@ __global__ __launch_bounds__(DEC_T) void k_decode(Dims dm, int P, const T* __res
       vn[b].get(vx[b]);
       lm[b] = lmn[b];
     }
+    const bool on = !TEST || eb + row < e1;
     if (eb + STEP < e1) fetch(eb + STEP);
 #pragma unroll
     for (int h = 0; h < HPG; ++h) {
@@ -217,17 +223,19 @@ __global__ __launch_bounds__(DEC_T) void k_decode(Dims dm, int P, const T* __res
         x[b] = entry_sum<D>(t) + lm[b];
         mn = fmaxf(mn, x[b]);
       }
-      const float c = __builtin_amdgcn_exp2f(m[h] - mn);
-      m[h] = mn;
-      s[h] *= c;
+      if (on) {
+        const float c = __builtin_amdgcn_exp2f(m[h] - mn);
+        m[h] = mn;
+        s[h] *= c;
 #pragma unroll
-      for (int j = 0; j < 8; ++j) o[h][j] *= c;
+        for (int j = 0; j < 8; ++j) o[h][j] *= c;
 #pragma unroll
-      for (int b = 0; b < EB; ++b) {
-        const float pe = __builtin_amdgcn_exp2f(x[b] - mn);
-        s[h] += pe;
+        for (int b = 0; b < EB; ++b) {
+          const float pe = __builtin_amdgcn_exp2f(x[b] - mn);
+          s[h] += pe;
 #pragma unroll
-        for (int j = 0; j < 8; ++j) o[h][j] += pe * vx[b][j];
+          for (int j = 0; j < 8; ++j) o[h][j] += pe * vx[b][j];
+        }
       }
     }
   }
@@ -235,7 +243,7 @@ __global__ __launch_bounds__(DEC_T) void k_decode(Dims dm, int P, const T* __res
 #pragma unroll
   for (int h = 0; h < HPG; ++h) {
     const float M = group_max<D>(m[h]);
-    const float c = m[h] == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(m[h] - M);
+    const float c = __builtin_amdgcn_exp2f(m[h] - M);
     const float S = group_sum<D>(s[h] * c);
     float oo[8];
 #pragma unroll
@@ -256,7 +264,7 @@ __global__ __launch_bounds__(DEC_T) void k_decode(Dims dm, int P, const T* __res
     float S = 0.f, O = 0.f;
 #pragma unroll
     for (int w2 = 0; w2 < DEC_W; ++w2) {
-      const float c = sM[w2][h] == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(sM[w2][h] - M);
+      const float c = __builtin_amdgcn_exp2f(sM[w2][h] - M);
       S += sS[w2][h] * c;
       O += sO[w2][h][dd] * c;
     }
@@ -281,7 +289,7 @@ __global__ __launch_bounds__(512) void k_decode_combine(Dims dm, int P, const fl
     for (int q2 = 0; q2 < P; ++q2) {
       const int64_t k = row0 + (int64_t)q2 * dm.hpg;
       const float2 ms = pml[k];
-      const float c = ms.x == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(ms.x - M);
+      const float c = __builtin_amdgcn_exp2f(ms.x - M);
       S += ms.y * c;
       O += po[k * D + dd] * c;
     }
