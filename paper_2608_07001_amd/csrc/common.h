@@ -435,6 +435,23 @@ __device__ __forceinline__ f32x4 mfma_bf16_16x16x32(s16x8 a, s16x8 b, f32x4 c) {
 // orders the wave's own LDS accesses (which the hardware keeps in order) for the compiler
 __device__ __forceinline__ void wave_lds_order() { asm volatile("" ::: "memory"); }
 
+// x = hi + mid + lo exactly, each a bf16, as three product operands
+__device__ __forceinline__ void split3x8(const float* x, uint4* part) {
+  uint32_t h[8], m[8], l[8];
+#pragma unroll
+  for (int r = 0; r < 8; ++r) {
+    h[r] = __float_as_uint(x[r]);
+    const float d1 = x[r] - __uint_as_float(h[r] & 0xffff0000u);
+    m[r] = __float_as_uint(d1);
+    l[r] = __float_as_uint(d1 - __uint_as_float(m[r] & 0xffff0000u));
+  }
+#define GKV_HI2(a, b) __builtin_amdgcn_perm((b), (a), 0x07060302u)
+  part[0] = make_uint4(GKV_HI2(h[0], h[1]), GKV_HI2(h[2], h[3]), GKV_HI2(h[4], h[5]), GKV_HI2(h[6], h[7]));
+  part[1] = make_uint4(GKV_HI2(m[0], m[1]), GKV_HI2(m[2], m[3]), GKV_HI2(m[4], m[5]), GKV_HI2(m[6], m[7]));
+  part[2] = make_uint4(GKV_HI2(l[0], l[1]), GKV_HI2(l[2], l[3]), GKV_HI2(l[4], l[5]), GKV_HI2(l[6], l[7]));
+#undef GKV_HI2
+}
+
 // A product's result read by a vector instruction in another basic block: the
 // compiler pads the wait for the matrix pipeline along one of the two paths into
 // the block only (seen where a wave-uniform branch follows the products: the

@@ -87,23 +87,6 @@ __device__ __forceinline__ float wave_scan(float v) {
   return v;
 }
 
-// x = hi + mid + lo exactly, each a bf16, as three product operands
-__device__ __forceinline__ void split3x8(const float* x, uint4* part) {
-  uint32_t h[8], m[8], l[8];
-#pragma unroll
-  for (int r = 0; r < 8; ++r) {
-    h[r] = __float_as_uint(x[r]);
-    const float d1 = x[r] - __uint_as_float(h[r] & 0xffff0000u);
-    m[r] = __float_as_uint(d1);
-    l[r] = __float_as_uint(d1 - __uint_as_float(m[r] & 0xffff0000u));
-  }
-#define GKV_HI2(a, b) __builtin_amdgcn_perm((b), (a), 0x07060302u)
-  part[0] = make_uint4(GKV_HI2(h[0], h[1]), GKV_HI2(h[2], h[3]), GKV_HI2(h[4], h[5]), GKV_HI2(h[6], h[7]));
-  part[1] = make_uint4(GKV_HI2(m[0], m[1]), GKV_HI2(m[2], m[3]), GKV_HI2(m[4], m[5]), GKV_HI2(m[6], m[7]));
-  part[2] = make_uint4(GKV_HI2(l[0], l[1]), GKV_HI2(l[2], l[3]), GKV_HI2(l[4], l[5]), GKV_HI2(l[6], l[7]));
-#undef GKV_HI2
-}
-
 // LV: the long nodes below the roots (mode BUILD_LONG or BUILD_LONG_FULL, list
 // `cls`), else the roots (mode BUILD_ROOT_SPLIT or BUILD_ROOT_FULL, items [first
 // of the class, its end) of the work list)
