@@ -1,4 +1,5 @@
-// Prototype-tree refinement of the units that need it.
+// Prototype-tree refinement of the units that need it, for fp32 caches (bf16: split.hip
+// and subtree.hip), and the work list of both.
 //
 // Implements App. A.3: RoPE-consistent key prototype eq:app_rope_prototype,
 // value prototype eq:app_value_prototype, effective multiplicity
@@ -12,7 +13,7 @@
 // those whose creating operation reaches the auction bound theta); one
 // workgroup per CU then drains the list.  Per unit (n <= 128 tokens, 512
 // threads):
-//   * staging: k° = RoPE^{-1}(k) of every token (fp32), V^T (bf16 or fp32),
+//   * staging: k° = RoPE^{-1}(k) of every token (fp32), V^T (fp32),
 //     R_t, A_t, curvature, ||k_t|| go to LDS; each wave keeps the quarter rows
 //     of its 16 distortion probes in registers;
 //   * per node [a, b) in BFS order: the candidate children are prefixes
@@ -26,8 +27,7 @@
 //       - M_q(child) = sum_t e_{q,t} v_t on the matrix cores: wave (probe tile,
 //         direction) recomputes e for a 16-token block (transposed logits, so e
 //         is already the B operand), accumulates M^T = V^T E^T piece by piece
-//         between cuts (e split into three bf16 parts: exact products), and at
-//         each cut turns the running sums into D_q for that child;
+//         between cuts and at each cut turns the running sums into D_q;
 //     then the fp32 scores decide (binary form wins ties, smaller cut wins
 //     ties) and the children are appended;
 //   * the node table is written back.
@@ -43,8 +43,7 @@ constexpr int CC = 2 * CM;       // child slots: prefix side [0, CM), suffix sid
 
 template <typename T, int D>
 struct RefLds {
-  static constexpr bool BF = sizeof(T) == 2;
-  static constexpr int LDV = BF ? NMAX + 8 : NMAX + 4;   // V^T row stride
+  static constexpr int LDV = sizeof(T) == 2 ? NMAX + 8 : NMAX + 4;   // V^T row stride
   static constexpr int KTS = D + 4;                       // k~ row stride
   static constexpr int oKo = 0;                           // k° [NMAX][D] fp32
   static constexpr int oVt = oKo + NMAX * D * 4;          // V^T [D][LDV]
@@ -102,26 +101,6 @@ struct Ref {
   }
   __device__ float* crow(int row) { return cs + row * CC; }
 };
-
-// x = hi + mid + lo exactly, each a bf16 (hi: top 8 significant bits by
-// truncation, mid: the next 8, lo: the rest), packed two per 32-bit word as
-// the matrix-core operands want them
-__device__ __forceinline__ void split3x4(const float* x, u32x2& hi, u32x2& mid, u32x2& lo) {
-  uint32_t h[4], m[4], l[4];
-#pragma unroll
-  for (int r = 0; r < 4; ++r) {
-    h[r] = __float_as_uint(x[r]) & 0xffff0000u;
-    const float r1 = x[r] - __uint_as_float(h[r]);
-    m[r] = __float_as_uint(r1) & 0xffff0000u;
-    l[r] = __float_as_uint(r1 - __uint_as_float(m[r]));
-  }
-#define GKV_HI2(a, b) __builtin_amdgcn_perm((b), (a), 0x07060302u)
-  hi.x = GKV_HI2(h[0], h[1]); hi.y = GKV_HI2(h[2], h[3]);
-  mid.x = GKV_HI2(m[0], m[1]); mid.y = GKV_HI2(m[2], m[3]);
-  lo.x = GKV_HI2(l[0], l[1]); lo.y = GKV_HI2(l[2], l[3]);
-#undef GKV_HI2
-}
-__device__ __forceinline__ s16x4 as_op(u32x2 v) { return __builtin_bit_cast(s16x4, v); }
 
 // ---------------------------------------------------------------------------
 // Prototype sums of both directions at once.  Group 0 reads the prefix
@@ -254,13 +233,11 @@ __device__ void proto_keys(Ref<T, D>& U, const Dims& dm, int64_t a0, int a, int 
 }
 
 // z_{q,c} = m_eff(c) exp(q . k~_c / sqrt(d) - m_q) for the wave's probe tile
-// and child tiles; A = probe rows (registers), B = k~ rows (fp32, split in three
-// bf16 parts for the bf16 path).
+// and child tiles; A = probe rows (registers), B = k~ rows.
 template <typename T, int D, int QW>
 __device__ void proto_attention(Ref<T, D>& U, const Dims& dm, int nl, int nr, const uint32_t* qreg, int pt,
                                 float scale) {
   using Lay = RefLds<T, D>;
-  constexpr bool BF = Lay::BF;
   constexpr int QE = D / 4;
   const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63, i16 = lane & 15, g4 = lane >> 4;
   if (16 * pt >= dm.W) return;
@@ -272,23 +249,8 @@ __device__ void proto_attention(Ref<T, D>& U, const Dims& dm, int nl, int nr, co
     if (!__any(cok)) continue;                // the tile holds no child to score (wave-uniform)
     const float* kt = U.Kt + gcc * Lay::KTS + QE * g4;
     f32x4 acc = {0.f, 0.f, 0.f, 0.f};
-    if constexpr (BF) {
 #pragma unroll
-      for (int s = 0; s < QE / 4; ++s) {
-        float x[4];
-        const float4 v = *(const float4*)(kt + 4 * s);
-        x[0] = cok ? v.x : 0.f; x[1] = cok ? v.y : 0.f; x[2] = cok ? v.z : 0.f; x[3] = cok ? v.w : 0.f;
-        u32x2 h, m, l;
-        split3x4(x, h, m, l);
-        const s16x4 qa = pk4(qreg[2 * s], qreg[2 * s + 1]);
-        acc = mfma_bf16_16x16x16(qa, as_op(l), acc);
-        acc = mfma_bf16_16x16x16(qa, as_op(m), acc);
-        acc = mfma_bf16_16x16x16(qa, as_op(h), acc);
-      }
-    } else {
-#pragma unroll
-      for (int s = 0; s < QE; ++s) acc = mfma_f32_16x16x4(__uint_as_float(qreg[s]), cok ? kt[s] : 0.f, acc);
-    }
+    for (int s = 0; s < QE; ++s) acc = mfma_f32_16x16x4(__uint_as_float(qreg[s]), cok ? kt[s] : 0.f, acc);
     // lane holds probes 16 pt + 4 g4 + r of child gc
     if (cok) {
       const float me = U.crow(3)[gc];
@@ -324,19 +286,11 @@ __device__ __forceinline__ void block_k(const T* __restrict__ Kp, int n, int blk
 template <typename T, int D, int QW>
 __device__ __forceinline__ void block_e(const uint32_t* kreg, int n, int blk, const uint32_t* qreg, float mq2,
                                         bool pok, float sc2, float* ev) {
-  constexpr bool BF = sizeof(T) == 2;
   constexpr int QE = D / 4;
   const int lane = threadIdx.x & 63, g4 = lane >> 4;
   f32x4 acc = {0.f, 0.f, 0.f, 0.f};
-  if constexpr (BF) {
 #pragma unroll
-    for (int s = 0; s < QE / 8; ++s)
-      acc = mfma_bf16_16x16x32(pk8(make_uint4(kreg[4 * s], kreg[4 * s + 1], kreg[4 * s + 2], kreg[4 * s + 3])),
-                               pk8(make_uint4(qreg[4 * s], qreg[4 * s + 1], qreg[4 * s + 2], qreg[4 * s + 3])), acc);
-  } else {
-#pragma unroll
-    for (int s = 0; s < QE; ++s) acc = mfma_f32_16x16x4(__uint_as_float(kreg[s]), __uint_as_float(qreg[s]), acc);
-  }
+  for (int s = 0; s < QE; ++s) acc = mfma_f32_16x16x4(__uint_as_float(kreg[s]), __uint_as_float(qreg[s]), acc);
 #pragma unroll
   for (int r = 0; r < 4; ++r) {
     const int t = 16 * blk + 4 * g4 + r;
@@ -352,7 +306,6 @@ __device__ void probe_sweeps(Ref<T, D>& U, const Dims& dm, const T* __restrict__
                              const int* XL, int nl, const int* XR, int nr, const uint32_t* qreg, int pt, float mq2,
                              float zc, float sc2) {
   using Lay = RefLds<T, D>;
-  constexpr bool BF = Lay::BF;
   constexpr int DT = D / 16;
   const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63, i16 = lane & 15, g4 = lane >> 4;
   const bool prefix = wave < 4;
@@ -365,9 +318,7 @@ __device__ void probe_sweeps(Ref<T, D>& U, const Dims& dm, const T* __restrict__
   for (int dt = 0; dt < DT; ++dt) M[dt] = f32x4{0.f, 0.f, 0.f, 0.f};
   float Z = 0.f;
   float ev[4] = {0.f, 0.f, 0.f, 0.f};
-  u32x2 eh = {0u, 0u}, em = {0u, 0u}, el = {0u, 0u};   // bf16 parts of the block's e
-  u32x2 vop[BF ? DT : 1];                             // V^T operands of the block (bf16)
-  float4 vf[BF ? 1 : DT];                             // ... (fp32)
+  float4 vf[DT];                                      // V^T operands of the block
   uint32_t kpre[QW];                                  // key quarter rows of the next block of the sweep
   int eblk = -1;
   const int lastblk = (n - 1) >> 4;
@@ -418,19 +369,9 @@ __device__ void probe_sweeps(Ref<T, D>& U, const Dims& dm, const T* __restrict__
         nb = nb < 0 ? 0 : (nb > lastblk ? lastblk : nb);
         block_k<T, D, QW>(Kp, n, nb, kpre);
         block_e<T, D, QW>(kreg, n, blk, qreg, mq2, pok, sc2, ev);
-        if constexpr (BF) {
-          split3x4(ev, eh, em, el);
 #pragma unroll
-          for (int dt = 0; dt < DT; ++dt) {
-            const uint2 vv = *(const uint2*)(U.Vt + (16 * dt + i16) * Lay::LDV + 16 * blk + 4 * g4);
-            vop[dt].x = vv.x;
-            vop[dt].y = vv.y;
-          }
-        } else {
-#pragma unroll
-          for (int dt = 0; dt < DT; ++dt)
-            vf[dt] = *(const float4*)(U.Vt + (16 * dt + i16) * Lay::LDV + 16 * blk + 4 * g4);
-        }
+        for (int dt = 0; dt < DT; ++dt)
+          vf[dt] = *(const float4*)(U.Vt + (16 * dt + i16) * Lay::LDV + 16 * blk + 4 * g4);
         eblk = blk;
       }
       const int t0 = 16 * blk + 4 * g4;
@@ -440,29 +381,15 @@ __device__ void probe_sweeps(Ref<T, D>& U, const Dims& dm, const T* __restrict__
         in[r] = t0 + r >= lo && t0 + r < hi;
         Z += in[r] ? ev[r] : 0.f;
       }
-      if constexpr (BF) {
-        u32x2 mk;
-        mk.x = (in[0] ? 0xffffu : 0u) | (in[1] ? 0xffff0000u : 0u);
-        mk.y = (in[2] ? 0xffffu : 0u) | (in[3] ? 0xffff0000u : 0u);
-        const s16x4 ph = as_op(eh & mk), pm = as_op(em & mk), pl = as_op(el & mk);
+      float emk[4];
 #pragma unroll
-        for (int dt = 0; dt < DT; ++dt) {
-          const s16x4 va = as_op(vop[dt]);
-          M[dt] = mfma_bf16_16x16x16(va, pl, M[dt]);
-          M[dt] = mfma_bf16_16x16x16(va, pm, M[dt]);
-          M[dt] = mfma_bf16_16x16x16(va, ph, M[dt]);
-        }
-      } else {
-        float emk[4];
+      for (int r = 0; r < 4; ++r) emk[r] = in[r] ? ev[r] : 0.f;
 #pragma unroll
-        for (int r = 0; r < 4; ++r) emk[r] = in[r] ? ev[r] : 0.f;
-#pragma unroll
-        for (int dt = 0; dt < DT; ++dt) {
-          M[dt] = mfma_f32_16x16x4(vf[dt].x, emk[0], M[dt]);
-          M[dt] = mfma_f32_16x16x4(vf[dt].y, emk[1], M[dt]);
-          M[dt] = mfma_f32_16x16x4(vf[dt].z, emk[2], M[dt]);
-          M[dt] = mfma_f32_16x16x4(vf[dt].w, emk[3], M[dt]);
-        }
+      for (int dt = 0; dt < DT; ++dt) {
+        M[dt] = mfma_f32_16x16x4(vf[dt].x, emk[0], M[dt]);
+        M[dt] = mfma_f32_16x16x4(vf[dt].y, emk[1], M[dt]);
+        M[dt] = mfma_f32_16x16x4(vf[dt].z, emk[2], M[dt]);
+        M[dt] = mfma_f32_16x16x4(vf[dt].w, emk[3], M[dt]);
       }
       if (prefix) cur = hi; else cur = lo;
     }
@@ -488,10 +415,9 @@ __global__ __launch_bounds__(BT) void k_refine(const Dims* __restrict__ dmp, int
   const Dims& dm = *dmp;
   const TreeView& tv = *tvp;
   using Lay = RefLds<T, D>;
-  constexpr bool BF = Lay::BF;
   constexpr int H2 = D / 2;
   constexpr int QE = D / 4;
-  constexpr int QW = BF ? QE / 2 : QE;
+  constexpr int QW = QE;
   extern __shared__ __align__(16) char smem[];
   Ref<T, D> U(smem);
   const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63, i16 = lane & 15, g4 = lane >> 4;
@@ -576,22 +502,11 @@ __global__ __launch_bounds__(BT) void k_refine(const Dims* __restrict__ dmp, int
         const float4 c0 = *(const float4*)(cosT + ta * H2 + c), c1 = *(const float4*)(cosT + ta * H2 + c + 4);
         const float4 s0 = *(const float4*)(sinT + ta * H2 + c), s1 = *(const float4*)(sinT + ta * H2 + c + 4);
         float k1[8], k2[8];
-        if constexpr (BF) {
-          const uint4 u1 = *(const uint4*)(Kp + (int64_t)t * D + c);
-          const uint4 u2 = *(const uint4*)(Kp + (int64_t)t * D + c + H2);
-          const uint32_t w1[4] = {u1.x, u1.y, u1.z, u1.w}, w2[4] = {u2.x, u2.y, u2.z, u2.w};
-#pragma unroll
-          for (int h = 0; h < 4; ++h) {
-            k1[2 * h] = __uint_as_float(w1[h] << 16); k1[2 * h + 1] = __uint_as_float(w1[h] & 0xffff0000u);
-            k2[2 * h] = __uint_as_float(w2[h] << 16); k2[2 * h + 1] = __uint_as_float(w2[h] & 0xffff0000u);
-          }
-        } else {
-          const float4* p1 = (const float4*)((const float*)Kp + (int64_t)t * D + c);
-          const float4* p2 = (const float4*)((const float*)Kp + (int64_t)t * D + c + H2);
-          const float4 a = p1[0], bq = p1[1], cq = p2[0], dq = p2[1];
-          k1[0] = a.x; k1[1] = a.y; k1[2] = a.z; k1[3] = a.w; k1[4] = bq.x; k1[5] = bq.y; k1[6] = bq.z; k1[7] = bq.w;
-          k2[0] = cq.x; k2[1] = cq.y; k2[2] = cq.z; k2[3] = cq.w; k2[4] = dq.x; k2[5] = dq.y; k2[6] = dq.z; k2[7] = dq.w;
-        }
+        const float4* p1 = (const float4*)((const float*)Kp + (int64_t)t * D + c);
+        const float4* p2 = (const float4*)((const float*)Kp + (int64_t)t * D + c + H2);
+        const float4 a = p1[0], bq = p1[1], cq = p2[0], dq = p2[1];
+        k1[0] = a.x; k1[1] = a.y; k1[2] = a.z; k1[3] = a.w; k1[4] = bq.x; k1[5] = bq.y; k1[6] = bq.z; k1[7] = bq.w;
+        k2[0] = cq.x; k2[1] = cq.y; k2[2] = cq.z; k2[3] = cq.w; k2[4] = dq.x; k2[5] = dq.y; k2[6] = dq.z; k2[7] = dq.w;
         const float cs8[8] = {c0.x, c0.y, c0.z, c0.w, c1.x, c1.y, c1.z, c1.w};
         const float sn8[8] = {s0.x, s0.y, s0.z, s0.w, s1.x, s1.y, s1.z, s1.w};
         float o1[8], o2[8];
@@ -614,33 +529,16 @@ __global__ __launch_bounds__(BT) void k_refine(const Dims* __restrict__ dmp, int
       }
       // V^T, zero past n
       const int rows16 = (n + 15) & ~15;
-      if constexpr (BF) {
-        constexpr int CPR = D / 8;
-        for (int e = tid; e < (rows16 / 2) * CPR; e += BT) {
-          const int grp = e / (8 * CPR), rem = e % (8 * CPR);
-          const int c = rem / 8, t = 2 * (8 * grp + rem % 8);
-          uint4 v0 = make_uint4(0, 0, 0, 0), v1 = v0;
-          if (t < n) v0 = *(const uint4*)(Vp + (int64_t)t * D + 8 * c);
-          if (t + 1 < n) v1 = *(const uint4*)(Vp + (int64_t)(t + 1) * D + 8 * c);
-          const uint32_t pa[4] = {v0.x, v0.y, v0.z, v0.w}, pb[4] = {v1.x, v1.y, v1.z, v1.w};
-#pragma unroll
-          for (int h = 0; h < 4; ++h) {
-            *(uint32_t*)(U.Vt + (8 * c + 2 * h) * Lay::LDV + t) = (pa[h] & 0xffffu) | (pb[h] << 16);
-            *(uint32_t*)(U.Vt + (8 * c + 2 * h + 1) * Lay::LDV + t) = (pa[h] >> 16) | (pb[h] & 0xffff0000u);
-          }
-        }
-      } else {
-        constexpr int CPR = D / 4;
-        for (int e = tid; e < rows16 * CPR; e += BT) {
-          const int grp = e / (16 * CPR), rem = e % (16 * CPR);
-          const int c = rem / 16, t = 16 * grp + rem % 16;
-          float4 vv = make_float4(0.f, 0.f, 0.f, 0.f);
-          if (t < n) vv = *(const float4*)((const float*)Vp + (int64_t)t * D + 4 * c);
-          U.Vt[(4 * c + 0) * Lay::LDV + t] = vv.x;
-          U.Vt[(4 * c + 1) * Lay::LDV + t] = vv.y;
-          U.Vt[(4 * c + 2) * Lay::LDV + t] = vv.z;
-          U.Vt[(4 * c + 3) * Lay::LDV + t] = vv.w;
-        }
+      constexpr int CPR = D / 4;
+      for (int e = tid; e < rows16 * CPR; e += BT) {
+        const int grp = e / (16 * CPR), rem = e % (16 * CPR);
+        const int c = rem / 16, t = 16 * grp + rem % 16;
+        float4 vv = make_float4(0.f, 0.f, 0.f, 0.f);
+        if (t < n) vv = *(const float4*)((const float*)Vp + (int64_t)t * D + 4 * c);
+        U.Vt[(4 * c + 0) * Lay::LDV + t] = vv.x;
+        U.Vt[(4 * c + 1) * Lay::LDV + t] = vv.y;
+        U.Vt[(4 * c + 2) * Lay::LDV + t] = vv.z;
+        U.Vt[(4 * c + 3) * Lay::LDV + t] = vv.w;
       }
       if (tid < n) {
         U.R[tid] = tv.tok_R[(int64_t)lg * dm.N_c + a0 + tid];

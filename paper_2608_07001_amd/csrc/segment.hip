@@ -719,8 +719,8 @@ __global__ void k_rz_score(Dims dm, const float* __restrict__ kappa, const float
 }
 
 // ---- K3: banded Gram --------------------------------------------------------
-// bf16: a workgroup owns 64 rows i0 .. i0+63 of one slab and the 192 rows
-// j in [i0 - 128, i0 + 64) they pair with; 64-dim chunks of those rows are
+// bf16: a workgroup owns 128 rows i0 .. i0+127 of one slab and the 256 rows
+// j in [i0 - 128, i0 + 128) they pair with; 64-dim chunks of those rows are
 // staged in LDS (double-buffered, 16-byte loads) and wave w accumulates the
 // 16 x 16 tiles (i-tile w, j-tile w .. w + 8) that touch the band.  A lane
 // supplies 16 consecutive dims of a chunk per operand (4 k-steps), so each
