@@ -313,16 +313,18 @@ __global__ __launch_bounds__(256) void k_curvature(Dims dm, const T* __restrict_
 // cores in three bf16 parts (six of the nine products; those left out are below
 // 2^-24 of |d||d'|).  (The Gram of the rows themselves would not do: d is a
 // difference of nearly equal unit vectors.)  Each sum is taken
-// in three levels, since the matrix cores' additions truncate: kappa is 8.7e-7 (rms)
-// from 64 bits as with the window sums, nearly all of it from the norms.  Bound by
-// the vector operations that form and split d and the barriers of each step; three
+// in three levels, since the matrix cores' additions truncate, and the forms in fp64:
+// kappa is 8.68e-7 (rms) from 64 bits at 32 heads of 128, 8.71e-7 with the window
+// sums, nearly all of it from the norms (runs of 256 columns and fp32 forms: more
+// than the window sums at a hidden size of 512, 3.76e-7 against 3.70e-7; now 3.67e-7).
+// Bound by the vector operations that form and split d and by the barriers; three
 // workgroups per CU (one LDS buffer) beat two with a second buffer, 1.6 against 2.0 ms.
 // A workgroup owns 128 rows t, eight 16-row tiles, stages the 32 rows before them as
 // well, and takes all columns or a part; a wave owns two tile rows against themselves
 // and the two tiles before, operands of the four tiles in registers.
 constexpr int DG_R = DG_I + DG_BAND;         // rows staged
 constexpr int DG_LD = DG_C + 8;              // LDS row stride (bf16)
-constexpr int DG_RUN = 8;                    // steps per run of products
+constexpr int DG_RUN = 4;                    // steps per run of products
 __global__ __launch_bounds__(256, 3) void k_dgram(Dims dm, const uint16_t* __restrict__ hidden, SegWs ws, int splits) {
   __shared__ __align__(16) uint16_t sh[3][DG_R * DG_LD];
   __shared__ float inv[DG_R + 1];
@@ -450,7 +452,7 @@ __global__ __launch_bounds__(256, 3) void k_dgram(Dims dm, const uint16_t* __res
 
 // kappa^{(l, w)} of 64 positions of a slab from the band (its column shares added in
 // order), and ||d_t||^2.  Four threads per position: the windows 4 and 8, and the
-// three forms of the window 16.  fp32 sums of products of one sign pattern.
+// three forms of the window 16.  The forms are summed in fp64.
 __global__ __launch_bounds__(256) void k_kappa(Dims dm, SegWs ws, int splits) {
   constexpr int R = CT + 2 * CHALO - 1;      // rows i0 - 15 .. i0 + 79
   constexpr int LD = DG_BAND + 1;
@@ -472,34 +474,34 @@ __global__ __launch_bounds__(256) void k_kappa(Dims dm, SegWs ws, int splits) {
   const int rc = p + CHALO - 1;              // staged row of d_i
   // ||delta_-||^2, ||delta_+||^2 and <delta_-, delta_+>, each times w^2
   auto minus2 = [&](int w) {
-    float v = 0.f;
+    double v = 0.0;
     for (int m = 0; m < w - 1; ++m) {
       const float* row = B + (rc - 1 - m) * LD;
-      float x = 0.f;
-      for (int k = m + 1; k < w - 1; ++k) x = fmaf((float)(w - 1 - k), row[k - m], x);
-      v = fmaf((float)(w - 1 - m), fmaf((float)(w - 1 - m), row[0], 2.f * x), v);
+      double x = 0.0;
+      for (int k = m + 1; k < w - 1; ++k) x = fma((double)(w - 1 - k), (double)row[k - m], x);
+      v = fma((double)(w - 1 - m), fma((double)(w - 1 - m), (double)row[0], 2.0 * x), v);
     }
-    return v;
+    return (float)v;
   };
   auto plus2 = [&](int w) {
-    float v = 0.f;
+    double v = 0.0;
     for (int k = 0; k < w; ++k) {            // the later of the two rows
       const float* row = B + (rc + k) * LD;
-      float x = 0.f;
-      for (int m = 0; m < k; ++m) x = fmaf((float)(w - m), row[k - m], x);
-      v = fmaf((float)(w - k), fmaf((float)(w - k), row[0], 2.f * x), v);
+      double x = 0.0;
+      for (int m = 0; m < k; ++m) x = fma((double)(w - m), (double)row[k - m], x);
+      v = fma((double)(w - k), fma((double)(w - k), (double)row[0], 2.0 * x), v);
     }
-    return v;
+    return (float)v;
   };
   auto cross = [&](int w) {
-    float v = 0.f;
+    double v = 0.0;
     for (int k = 0; k < w; ++k) {
       const float* row = B + (rc + k) * LD;
-      float x = 0.f;
-      for (int m = 0; m < w - 1; ++m) x = fmaf((float)(w - 1 - m), row[k + 1 + m], x);
-      v = fmaf((float)(w - k), x, v);
+      double x = 0.0;
+      for (int m = 0; m < w - 1; ++m) x = fma((double)(w - 1 - m), (double)row[k + 1 + m], x);
+      v = fma((double)(w - k), x, v);
     }
-    return v;
+    return (float)v;
   };
   const int64_t i = i0 + p;
   auto put = [&](int wi, int w, float mm, float pp, float mp) {
