@@ -121,8 +121,9 @@ __device__ __forceinline__ float group_sum(float v) {
 __host__ __device__ constexpr int dec_block(bool bf16) { return bf16 ? 1 : 2; }
 // Whether an entry past the end is skipped by a test, or takes part with the logit
 // -inf.  The test costs more where its branch splits many heads' work: eight heads
-// 309.8 -> 295.9 us without it (32 K tokens, 4x), four of 128 297 with either, but
-// 0.8 % more at 128 K; a block of two has one test for both and cannot use it.
+// 309.8 -> 295.9 us without it (32 K tokens, 4x); four of 128 943.8 with, 951 without
+// (128 K).  A block of two has no one test.  The tested loop is kept apart: written
+// as a block of one it was 2.4 % slower for a short cache (64.8 -> 66.4 us).
 __host__ __device__ constexpr bool dec_test(bool bf16, int hpg) { return bf16 && hpg < 8; }
 
 template <typename T, int D, int HPG>
@@ -157,9 +158,9 @@ __global__ __launch_bounds__(DEC_T) void k_decode(Dims dm, int P, const T* __res
 #pragma unroll
     for (int j = 0; j < 8; ++j) qv[h][j] *= sc2;
   }
-  // the least finite logit: a state that has seen nothing, or only an absent entry
-  // (logit -inf), stays (NONE, 0, 0)
-  constexpr float NONE = -FLT_MAX;
+  // without the test, the least finite logit: a state that has seen nothing, or only
+  // an absent entry (logit -inf), stays (NONE, 0, 0)
+  constexpr float NONE = TEST ? -INFINITY : -FLT_MAX;
   float m[HPG], s[HPG], o[HPG][8];
 #pragma unroll
   for (int h = 0; h < HPG; ++h) {
@@ -181,49 +182,91 @@ __global__ __launch_bounds__(DEC_T) void k_decode(Dims dm, int P, const T* __res
       lm = 0.f;
     }
   };
-  // EB entries per lane group at a time, the next ones in flight: one maximum and
-  // one rescaling of the running state for all of them.  Wave-uniform trip count;
-  // an entry past e1 contributes nothing.
-  constexpr int64_t STEP = (int64_t)DEC_W * EPW * EB;
-  Raw8<T> kn[EB], vn[EB];
-  float lmn[EB];
-  auto fetch = [&](int64_t eb) {
-#pragma unroll
-    for (int b = 0; b < EB; ++b) {
-      const int64_t e = eb + b * EPW + row;
+  if constexpr (TEST) {
+    // wave-uniform trip count; a lane group past e1 contributes nothing
+    constexpr int64_t STEP = (int64_t)DEC_W * EPW;
+    Raw8<T> kn, vn;
+    float lmn = 0.f;
+    {
+      const int64_t e = e0 + (int64_t)w * EPW + row;
       const T* kr;
       const T* vr;
-      locate(e < e1 ? e : e0, kr, vr, lmn[b]);
-      if (!TEST && e >= e1) lmn[b] = -INFINITY;
-      kn[b].load(kr + 8 * sub);
-      vn[b].load(vr + 8 * sub);
+      locate(e < e1 ? e : e0, kr, vr, lmn);
+      if (e0 < e1) { kn.load(kr + 8 * sub); vn.load(vr + 8 * sub); }
     }
-  };
-  const int64_t w0 = e0 + (int64_t)w * EPW * EB;
-  if (w0 < e1) fetch(w0);
-  for (int64_t eb = w0; eb < e1; eb += STEP) {
-    float kx[EB][8], vx[EB][8], lm[EB];
+    for (int64_t eb = e0 + (int64_t)w * EPW; eb < e1; eb += STEP) {
+      const bool on = eb + row < e1;
+      float kx[8], vx[8];
+      kn.get(kx);
+      vn.get(vx);
+      const float lm = lmn;
+      if (eb + STEP < e1) {                     // the next entry of this lane group, in flight
+        const int64_t e = eb + STEP + row;
+        const T* kr;
+        const T* vr;
+        locate(e < e1 ? e : e0, kr, vr, lmn);
+        kn.load(kr + 8 * sub);
+        vn.load(vr + 8 * sub);
+      }
 #pragma unroll
-    for (int b = 0; b < EB; ++b) {
-      kn[b].get(kx[b]);
-      vn[b].get(vx[b]);
-      lm[b] = lmn[b];
+      for (int h = 0; h < HPG; ++h) {
+        float x = 0.f;
+#pragma unroll
+        for (int j = 0; j < 8; ++j) x += qv[h][j] * kx[j];
+        x = entry_sum<D>(x) + lm;
+        if (on) {
+          const float mn = fmaxf(m[h], x);
+          const float c = __builtin_amdgcn_exp2f(m[h] - mn);
+          const float pe = __builtin_amdgcn_exp2f(x - mn);
+          s[h] = s[h] * c + pe;
+#pragma unroll
+          for (int j = 0; j < 8; ++j) o[h][j] = o[h][j] * c + pe * vx[j];
+          m[h] = mn;
+        }
+      }
     }
-    const bool on = !TEST || eb + row < e1;
-    if (eb + STEP < e1) fetch(eb + STEP);
-#pragma unroll
-    for (int h = 0; h < HPG; ++h) {
-      float x[EB];
-      float mn = m[h];
+  } else {
+    // EB entries per lane group at a time, the next ones in flight: one maximum and
+    // one rescaling of the running state for all of them.  Wave-uniform trip count;
+    // an entry past e1 contributes nothing.
+    constexpr int64_t STEP = (int64_t)DEC_W * EPW * EB;
+    Raw8<T> kn[EB], vn[EB];
+    float lmn[EB];
+    auto fetch = [&](int64_t eb) {
 #pragma unroll
       for (int b = 0; b < EB; ++b) {
-        float t = 0.f;
-#pragma unroll
-        for (int j = 0; j < 8; ++j) t += qv[h][j] * kx[b][j];
-        x[b] = entry_sum<D>(t) + lm[b];
-        mn = fmaxf(mn, x[b]);
+        const int64_t e = eb + b * EPW + row;
+        const T* kr;
+        const T* vr;
+        locate(e < e1 ? e : e0, kr, vr, lmn[b]);
+        if (e >= e1) lmn[b] = -INFINITY;
+        kn[b].load(kr + 8 * sub);
+        vn[b].load(vr + 8 * sub);
       }
-      if (on) {
+    };
+    const int64_t w0 = e0 + (int64_t)w * EPW * EB;
+    if (w0 < e1) fetch(w0);
+    for (int64_t eb = w0; eb < e1; eb += STEP) {
+      float kx[EB][8], vx[EB][8], lm[EB];
+#pragma unroll
+      for (int b = 0; b < EB; ++b) {
+        kn[b].get(kx[b]);
+        vn[b].get(vx[b]);
+        lm[b] = lmn[b];
+      }
+      if (eb + STEP < e1) fetch(eb + STEP);
+#pragma unroll
+      for (int h = 0; h < HPG; ++h) {
+        float x[EB];
+        float mn = m[h];
+#pragma unroll
+        for (int b = 0; b < EB; ++b) {
+          float t = 0.f;
+#pragma unroll
+          for (int j = 0; j < 8; ++j) t += qv[h][j] * kx[b][j];
+          x[b] = entry_sum<D>(t) + lm[b];
+          mn = fmaxf(mn, x[b]);
+        }
         const float c = __builtin_amdgcn_exp2f(m[h] - mn);
         m[h] = mn;
         s[h] *= c;
@@ -243,7 +286,7 @@ __global__ __launch_bounds__(DEC_T) void k_decode(Dims dm, int P, const T* __res
 #pragma unroll
   for (int h = 0; h < HPG; ++h) {
     const float M = group_max<D>(m[h]);
-    const float c = __builtin_amdgcn_exp2f(m[h] - M);
+    const float c = m[h] == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(m[h] - M);
     const float S = group_sum<D>(s[h] * c);
     float oo[8];
 #pragma unroll
@@ -264,7 +307,7 @@ __global__ __launch_bounds__(DEC_T) void k_decode(Dims dm, int P, const T* __res
     float S = 0.f, O = 0.f;
 #pragma unroll
     for (int w2 = 0; w2 < DEC_W; ++w2) {
-      const float c = __builtin_amdgcn_exp2f(sM[w2][h] - M);
+      const float c = sM[w2][h] == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(sM[w2][h] - M);
       S += sS[w2][h] * c;
       O += sO[w2][h][dd] * c;
     }
@@ -289,7 +332,7 @@ __global__ __launch_bounds__(512) void k_decode_combine(Dims dm, int P, const fl
     for (int q2 = 0; q2 < P; ++q2) {
       const int64_t k = row0 + (int64_t)q2 * dm.hpg;
       const float2 ms = pml[k];
-      const float c = __builtin_amdgcn_exp2f(ms.x - M);
+      const float c = ms.x == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(ms.x - M);
       S += ms.y * c;
       O += po[k * D + dd] * c;
     }
