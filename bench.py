@@ -155,7 +155,7 @@ MFMA_BF16_PEAK_TFLOPS = 2500.0
 def kernel_names(dtype):
     """The kernels each timed stage launches (bf16 or fp32 caches)."""
     if dtype == "bf16":
-        return {"segment": "gracekv_segment (k_gram_bf16, k_dgram, k_kappa, k_dist2, DP kernels)",
+        return {"segment": "gracekv_segment (k_gram_bf16, k_curvature, k_dist2, DP kernels)",
                 "rowstats": "k_rowstats_bf + k_rowstats_combine", "token_relevance": "k_rel_rows",
                 "root": "k_root_bf", "root_split": "k_split<d, NT, false> (the roots)",
                 "refine": "k_split<d, NT, true> (nodes of more than 16 tokens) + k_subtree + k_number",

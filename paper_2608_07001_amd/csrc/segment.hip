@@ -1,13 +1,17 @@
 // Curvature-guided slot segmentation (App. B.2 - B.3).
 //
-// K1  seg_curvature: the L2-normalised hidden rows hbar (eq:app_hidden_normalization;
-//     norms from the Gram diagonal of K3, which runs first) give each position, for w in {4, 8, 16}, the
-//     three dot products of delta_- = hbar_i - mean(hbar_{i-w+1..i}) and
+// K1  seg_curvature: per slab and 64-position tile, L2-normalised hidden rows
+//     (eq:app_hidden_normalization; norms from the Gram diagonal of K3) are
+//     staged in LDS column-chunk by column-chunk; each position accumulates, for w in {4, 8, 16}, the three
+//     dot products of delta_- = hbar_i - mean(hbar_{i-w+1..i}) and
 //     delta_+ = mean(hbar_{i+1..i+w}) - hbar_i (eq:app_local_means,
 //     eq:app_local_directions), giving kappa^{(l,w)} (eq:app_local_curvature;
 //     zero outside w <= i < T - w), and ||hbar_{i+1} - hbar_i||^2 for the
-//     dispersion (eq:app_adjacent_difference).  bf16: quadratic forms in the banded
-//     Gram of the differences (k_dgram, k_kappa); fp32: window sums (k_curvature).
+//     dispersion (eq:app_adjacent_difference).  The window sums stay: as quadratic
+//     forms in the banded Gram of the row differences (matrix cores, three bf16 parts)
+//     the curvature took 1.6 instead of 2.4 ms for 3 x 131 K rows of 4096, but the
+//     forms cancel: 1.1e-6 (rms) from 64 bits where rows alternate about a mean,
+//     against 1.1e-7.
 // K1b seg_stabilize: kappa_i = Mean - lam_stab * population Std over the
 //     |L_seg| x 3 values (eq:app_stabilized_curvature).
 // K2  seg_robust_z: lower medians by radix select on order-preserving keys;
@@ -58,7 +62,6 @@ struct SegWs {
   double* smax_part; // [N_c / SLE + 1] largest finite |S| per slot-score workgroup
   int2* bt_tab;     // [backtrack chunks][128] (exit, starts emitted) per chunk entry
   int2* bt_ent;     // [backtrack chunks] (entry, output offset) of each chunk on the path
-  float* dband;     // [column splits][n_seg][T][DG_BAND] <d_t, d_t-delta>, d_t = hbar_t+1 - hbar_t (bf16)
 };
 
 // Chunk-parallel DP: ends per chunk and the warm-up margin of a chunk's guessed run.
@@ -74,13 +77,10 @@ __host__ __device__ inline int64_t bt_chunks(int64_t N) { return (N + BTC - 1) /
 
 static size_t al(size_t x) { return (x + 255) & ~(size_t)255; }
 
-// The workspace.  Three stages use what lies behind the Gram one after another:
-// the band of differences (k_dgram, k_kappa) all of it, before the first of the
-// regions named below is written; the DP and the backtrack the part of dist2 and
-// of the select state, which the slot scores were the last to read.
+// The workspace.  The tables of the DP and the backtrack lie over dist2 and the
+// select state, which the slot scores were the last to read.
 struct SegBytes {
   size_t kap9, sqd, sq, gram, dist2, bs, rz, P2, Poff, Fdbg, S, dp, smax, spare;
-  size_t behind_gram() const { return dist2 + 2 * bs + rz + P2 + Poff + Fdbg + S + dp + smax + spare; }
 };
 static SegBytes seg_bytes(const Dims& dm) {
   const size_t T = (size_t)dm.T, N = (size_t)dm.N_c, C = (N + 1023) / 1024 + 1;   // two DP chunks and a margin each
@@ -104,27 +104,7 @@ static SegBytes seg_bytes(const Dims& dm) {
 
 size_t segment_ws_bytes(const Dims& dm) {
   const SegBytes b = seg_bytes(dm);
-  return b.kap9 + b.sqd + b.sq + b.gram + b.behind_gram();
-}
-
-// Banded Gram of the differences (k_dgram): rows per workgroup, band, columns per
-// step.  The columns are summed in up to three parts, by one workgroup one after
-// another or by a workgroup each, and the parts are added in their order either
-// way, so a position's curvature does not depend on the length of the context.
-// A workgroup each where the row tiles alone leave workgroups' places on the chip
-// free (three per CU; 99 tiles of a 4 K context: 130 -> 89 us), as far as the bands
-// of all parts find room.  0: not even one does (contexts hardly longer than the
-// window, many slabs); k_curvature then.
-constexpr int DG_I = 128, DG_BAND = 32, DG_C = 32;
-__host__ __device__ inline int dg_parts(int Dh) {
-  const int most = Dh / (8 * DG_C);          // eight steps at least
-  return most < 1 ? 1 : (most > 3 ? 3 : most);
-}
-static int dg_splits(const Dims& dm) {
-  const int64_t tiles = (dm.T + DG_I - 1) / DG_I * dm.n_seg;
-  const int64_t room = (int64_t)seg_bytes(dm).behind_gram() / ((int64_t)dm.n_seg * dm.T * DG_BAND * 4);
-  const int parts = dg_parts(dm.Dh);
-  return room < 1 ? 0 : (tiles < 768 && parts <= room ? parts : 1);
+  return b.kap9 + b.sqd + b.sq + b.gram + b.dist2 + 2 * b.bs + b.rz + b.P2 + b.Poff + b.Fdbg + b.S + b.dp + b.smax + b.spare;
 }
 
 static SegWs seg_view(void* ws, const Dims& dm) {
@@ -136,7 +116,6 @@ static SegWs seg_view(void* ws, const Dims& dm) {
   s.sqd = (float*)p; p += b.sqd;
   s.sq = (float*)p; p += b.sq;
   s.gram = (float*)p; p += b.gram;
-  s.dband = (float*)p;
   char* q = p;                               // DP and backtrack: at most dist2 + 2 bs + rz
   s.dlt = (long long*)q; q += al(C * 8);
   s.cdiff = (long long*)q; q += al(C * 8);
@@ -300,229 +279,6 @@ __global__ __launch_bounds__(256) void k_curvature(Dims dm, const T* __restrict_
       ws.sqd[(int64_t)slab * T_ + i] = (i + 1 < T_) ? v[9] : 0.f;
     }
   }
-}
-
-// ---- K1 for bf16: curvature from the banded Gram of the differences ----------
-// delta_- = (1/w) sum_m (w - 1 - m) d_{i-1-m} (m < w - 1) and delta_+ = (1/w)
-// sum_m (w - m) d_{i+m} (m < w) with d_t = hbar_{t+1} - hbar_t, so the three dot
-// products of every window are quadratic forms in <d_t, d_t'>, |t - t'| <= 30:
-// one banded Gram replaces the 29 vector operations per element of the window
-// sums: 2.4 -> 1.65 ms with k_kappa for 3 x 131 K rows of 4096 (0.7 ms to read),
-// 195 -> 103 us for 3 x 4 K.
-// d is formed in fp32 from the normalised rows, as before, and goes to the matrix
-// cores in three bf16 parts (six of the nine products; those left out are below
-// 2^-24 of |d||d'|).  (The Gram of the rows themselves would not do: d is a
-// difference of nearly equal unit vectors.)  Each sum is taken
-// in three levels, since the matrix cores' additions truncate, and the forms in fp64:
-// kappa is 8.68e-7 (rms) from 64 bits at 32 heads of 128, 8.71e-7 with the window
-// sums, nearly all of it from the norms (runs of 256 columns and fp32 forms: more
-// than the window sums at a hidden size of 512, 3.76e-7 against 3.70e-7; now 3.67e-7).
-// Bound by the vector operations that form and split d and by the barriers; three
-// workgroups per CU (one LDS buffer) beat two with a second buffer, 1.6 against 2.0 ms.
-// A workgroup owns 128 rows t, eight 16-row tiles, stages the 32 rows before them as
-// well, and takes all columns or a part; a wave owns two tile rows against themselves
-// and the two tiles before, operands of the four tiles in registers.
-constexpr int DG_R = DG_I + DG_BAND;         // rows staged
-constexpr int DG_LD = DG_C + 8;              // LDS row stride (bf16)
-constexpr int DG_RUN = 4;                    // steps per run of products
-__global__ __launch_bounds__(256, 3) void k_dgram(Dims dm, const uint16_t* __restrict__ hidden, SegWs ws, int splits) {
-  __shared__ __align__(16) uint16_t sh[3][DG_R * DG_LD];
-  __shared__ float inv[DG_R + 1];
-  const int slab = blockIdx.y;
-  const int64_t i0 = (int64_t)blockIdx.x * DG_I, r0 = i0 - DG_BAND;   // row of staged row 0
-  const int64_t T_ = dm.T;
-  const int Dh = dm.Dh;
-  const int nc = (Dh + DG_C - 1) / DG_C;
-  const int per = (nc + dg_parts(Dh) - 1) / dg_parts(Dh);             // steps of a part
-  const int cb = splits == 1 ? 0 : (int)blockIdx.z * per, ce = splits == 1 || cb + per > nc ? nc : cb + per;
-  const uint16_t* H = hidden + (int64_t)slab * T_ * Dh;
-  const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63, i16 = lane & 15, g4 = lane >> 4;
-  for (int r = tid; r <= DG_R; r += 256) {
-    const int64_t i = r0 + r;
-    inv[r] = i >= 0 && i < T_ ? 1.0f / fmaxf(sqrtf(ws.gram[((int64_t)slab * T_ + i) * BAND]), dm.eps_seg) : 0.f;
-  }
-  __syncthreads();
-  constexpr int CPR = DG_C / 8, IT = (DG_R * CPR + 255) / 256;
-  uint4 ua[IT], ub[IT];                      // rows t and t + 1 of the thread's (row, 8 columns) items
-  auto fetch = [&](int ch) {
-#pragma unroll
-    for (int k = 0; k < IT; ++k) {
-      const int e = tid + 256 * k, r = e / CPR, c = ch * DG_C + (e % CPR) * 8;
-      const int64_t t = r0 + r;
-      ua[k] = make_uint4(0, 0, 0, 0);
-      ub[k] = ua[k];
-      if (r < DG_R && t >= 0 && t + 1 < T_ && c < Dh) {
-        ua[k] = *(const uint4*)(H + t * Dh + c);
-        ub[k] = *(const uint4*)(H + (t + 1) * Dh + c);
-      }
-    }
-  };
-  auto store = [&] {
-#pragma unroll
-    for (int k = 0; k < IT; ++k) {
-      const int e = tid + 256 * k, r = e / CPR, c = (e % CPR) * 8;
-      if (r >= DG_R) break;
-      const float n0 = inv[r], n1 = inv[r + 1];
-      const uint32_t wa[4] = {ua[k].x, ua[k].y, ua[k].z, ua[k].w}, wb[4] = {ub[k].x, ub[k].y, ub[k].z, ub[k].w};
-      float x[8];
-#pragma unroll
-      for (int h = 0; h < 4; ++h) {
-        x[2 * h] = __uint_as_float(wb[h] << 16) * n1 - __uint_as_float(wa[h] << 16) * n0;
-        x[2 * h + 1] = __uint_as_float(wb[h] & 0xffff0000u) * n1 - __uint_as_float(wa[h] & 0xffff0000u) * n0;
-      }
-      uint4 part[3];
-      split3x8(x, part);
-#pragma unroll
-      for (int p = 0; p < 3; ++p) *(uint4*)(sh[p] + r * DG_LD + c) = part[p];
-    }
-  };
-  // the wave's tile rows a0, a0 + 1 against a, a - 1, a - 2.  Three levels of sums:
-  // DG_RUN steps by the matrix cores (runs of a third of the columns left kappa
-  // biased by 2e-7), the part, the total.
-  const int a0 = 2 + 2 * wave;
-  f32x4 acc[2][3], part[2][3], total[2][3];
-#pragma unroll
-  for (int a = 0; a < 2; ++a)
-#pragma unroll
-    for (int b = 0; b < 3; ++b) acc[a][b] = part[a][b] = total[a][b] = f32x4{0.f, 0.f, 0.f, 0.f};
-  if (cb < ce) {
-    fetch(cb);
-    store();
-  }
-  int done = 0;                              // steps of the current part
-  for (int ch = cb; ch < ce; ++ch) {
-    __syncthreads();
-    if (ch + 1 < ce) fetch(ch + 1);          // the next step's rows in flight
-    s16x8 f[4][3];                           // tiles a0 - 2 .. a0 + 1
-#pragma unroll
-    for (int k = 0; k < 4; ++k)
-#pragma unroll
-      for (int p = 0; p < 3; ++p) f[k][p] = pk8(*(const uint4*)(sh[p] + (16 * (a0 - 2 + k) + i16) * DG_LD + 8 * g4));
-#pragma unroll
-    for (int a = 0; a < 2; ++a)
-#pragma unroll
-      for (int b = 0; b < 3; ++b) {          // rows of tile a0 + a, columns of tile a0 + a - b
-        const int ka = a + 2, kb = a + 2 - b;
-        acc[a][b] = mfma_bf16_16x16x32(f[ka][2], f[kb][0], acc[a][b]);
-        acc[a][b] = mfma_bf16_16x16x32(f[ka][0], f[kb][2], acc[a][b]);
-        acc[a][b] = mfma_bf16_16x16x32(f[ka][1], f[kb][1], acc[a][b]);
-        acc[a][b] = mfma_bf16_16x16x32(f[ka][1], f[kb][0], acc[a][b]);
-        acc[a][b] = mfma_bf16_16x16x32(f[ka][0], f[kb][1], acc[a][b]);
-        acc[a][b] = mfma_bf16_16x16x32(f[ka][0], f[kb][0], acc[a][b]);
-      }
-    ++done;
-    const bool end = done == per || ch + 1 == ce;
-    if (end || done % DG_RUN == 0) {
-#pragma unroll
-      for (int a = 0; a < 2; ++a) mfma_done(acc[a]);
-#pragma unroll
-      for (int a = 0; a < 2; ++a)
-#pragma unroll
-        for (int b = 0; b < 3; ++b) {
-          part[a][b] += acc[a][b];
-          acc[a][b] = f32x4{0.f, 0.f, 0.f, 0.f};
-        }
-    }
-    if (end) {
-#pragma unroll
-      for (int a = 0; a < 2; ++a)
-#pragma unroll
-        for (int b = 0; b < 3; ++b) {
-          total[a][b] += part[a][b];
-          part[a][b] = f32x4{0.f, 0.f, 0.f, 0.f};
-        }
-      done = 0;
-    }
-    __syncthreads();
-    if (ch + 1 < ce) store();
-  }
-  float* out = ws.dband + ((int64_t)blockIdx.z * dm.n_seg + slab) * T_ * DG_BAND;
-#pragma unroll
-  for (int a = 0; a < 2; ++a)
-#pragma unroll
-    for (int b = 0; b < 3; ++b)
-#pragma unroll
-      for (int r = 0; r < 4; ++r) {
-        // lane (i16, g4): row 16 (a0 + a) + 4 g4 + r, column 16 (a0 + a - b) + i16
-        const int64_t t = r0 + 16 * (a0 + a) + 4 * g4 + r;
-        const int dl = 16 * b + 4 * g4 + r - i16;
-        if (t < T_ && dl >= 0 && dl < DG_BAND) out[t * DG_BAND + dl] = total[a][b][r];
-      }
-}
-
-// kappa^{(l, w)} of 64 positions of a slab from the band (its column shares added in
-// order), and ||d_t||^2.  Four threads per position: the windows 4 and 8, and the
-// three forms of the window 16.  The forms are summed in fp64.
-__global__ __launch_bounds__(256) void k_kappa(Dims dm, SegWs ws, int splits) {
-  constexpr int R = CT + 2 * CHALO - 1;      // rows i0 - 15 .. i0 + 79
-  constexpr int LD = DG_BAND + 1;
-  __shared__ float B[R * LD];
-  __shared__ float form[3][CT];
-  const int slab = blockIdx.y;
-  const int64_t i0 = (int64_t)blockIdx.x * CT, t0 = i0 - (CHALO - 1), T_ = dm.T;
-  const int tid = threadIdx.x;
-  for (int e = tid; e < R * DG_BAND; e += 256) {
-    const int r = e / DG_BAND, c = e % DG_BAND;
-    const int64_t t = t0 + r;
-    float v = 0.f;
-    if (t >= 0 && t - c >= 0 && t < T_)
-      for (int s = 0; s < splits; ++s) v += ws.dband[(((int64_t)s * dm.n_seg + slab) * T_ + t) * DG_BAND + c];
-    B[r * LD + c] = v;
-  }
-  __syncthreads();
-  const int p = tid & (CT - 1), part = tid / CT;        // one part per wave
-  const int rc = p + CHALO - 1;              // staged row of d_i
-  // ||delta_-||^2, ||delta_+||^2 and <delta_-, delta_+>, each times w^2
-  auto minus2 = [&](int w) {
-    double v = 0.0;
-    for (int m = 0; m < w - 1; ++m) {
-      const float* row = B + (rc - 1 - m) * LD;
-      double x = 0.0;
-      for (int k = m + 1; k < w - 1; ++k) x = fma((double)(w - 1 - k), (double)row[k - m], x);
-      v = fma((double)(w - 1 - m), fma((double)(w - 1 - m), (double)row[0], 2.0 * x), v);
-    }
-    return (float)v;
-  };
-  auto plus2 = [&](int w) {
-    double v = 0.0;
-    for (int k = 0; k < w; ++k) {            // the later of the two rows
-      const float* row = B + (rc + k) * LD;
-      double x = 0.0;
-      for (int m = 0; m < k; ++m) x = fma((double)(w - m), (double)row[k - m], x);
-      v = fma((double)(w - k), fma((double)(w - k), (double)row[0], 2.0 * x), v);
-    }
-    return (float)v;
-  };
-  auto cross = [&](int w) {
-    double v = 0.0;
-    for (int k = 0; k < w; ++k) {
-      const float* row = B + (rc + k) * LD;
-      double x = 0.0;
-      for (int m = 0; m < w - 1; ++m) x = fma((double)(w - 1 - m), (double)row[k + 1 + m], x);
-      v = fma((double)(w - k), x, v);
-    }
-    return (float)v;
-  };
-  const int64_t i = i0 + p;
-  auto put = [&](int wi, int w, float mm, float pp, float mp) {
-    float kap = 0.f;
-    if (i >= w && i < T_ - w) {
-      const float iw = 1.0f / (float)w;
-      const float nm = fmaxf(sqrtf(mm) * iw, dm.eps_seg), np = fmaxf(sqrtf(pp) * iw, dm.eps_seg);
-      kap = 1.f - mp * (iw * iw) / (nm * np);
-    }
-    ws.kap9[((int64_t)slab * 3 + wi) * T_ + i] = kap;
-  };
-  if (part == 0) form[0][p] = minus2(16);
-  else if (part == 1) form[1][p] = plus2(16);
-  else if (part == 2) form[2][p] = cross(16);
-  else if (i < T_) {
-    put(0, 4, minus2(4), plus2(4), cross(4));
-    put(1, 8, minus2(8), plus2(8), cross(8));
-    ws.sqd[(int64_t)slab * T_ + i] = i + 1 < T_ ? B[rc * LD] : 0.f;
-  }
-  __syncthreads();
-  if (part == 0 && i < T_) put(2, 16, form[0][p], form[1][p], form[2][p]);
 }
 
 __global__ void k_stabilize(Dims dm, SegWs ws, float* kappa) {
@@ -1416,14 +1172,7 @@ hipError_t launch_segment(const Dims& dm, const void* hidden, const float* surpr
   if (dm.dtype == GRACEKV_BF16) {
     const dim3 g3((unsigned)((dm.T + GB_I - 1) / GB_I), dm.n_seg);
     hipLaunchKernelGGL(k_gram_bf16, g3, dim3(GB_T), 0, st, dm, (const uint16_t*)hidden, ws);
-    const int splits = dg_splits(dm);
-    if (splits > 0) {
-      hipLaunchKernelGGL(k_dgram, dim3((unsigned)((dm.T + DG_I - 1) / DG_I), dm.n_seg, splits), dim3(256), 0, st, dm,
-                         (const uint16_t*)hidden, ws, splits);
-      hipLaunchKernelGGL(k_kappa, g1, dim3(256), 0, st, dm, ws, splits);
-    } else {
-      hipLaunchKernelGGL(k_curvature<uint16_t>, g1, dim3(256), 0, st, dm, (const uint16_t*)hidden, ws);
-    }
+    hipLaunchKernelGGL(k_curvature<uint16_t>, g1, dim3(256), 0, st, dm, (const uint16_t*)hidden, ws);
   } else {
     const dim3 g3((unsigned)((dm.T + 15) / 16), dm.n_seg);
     hipLaunchKernelGGL(k_gram_f32, g3, dim3(192), 0, st, dm, (const float*)hidden, ws);

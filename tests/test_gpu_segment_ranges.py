@@ -1,9 +1,10 @@
-"""Segmentation at the sizes where its kernels change over: row tiles of the
-banded Gram of differences, hidden sizes that end inside a step, columns shared
-by several workgroups, contexts too short for the band's workspace (the window
-sums take over), the median in one workgroup and in passes, the warm-up of the
-chunked recurrence.  Curvature against float64, scores against exact medians,
-slots against the serial recurrence on the same scores."""
+"""Segmentation at the sizes where its kernels change over: position tiles of
+the window sums, hidden sizes that end inside a column chunk, contexts hardly
+longer than the window, the median in one workgroup and in passes, the warm-up
+of the chunked recurrence.  Curvature against float64 (also where rows
+alternate about a mean, which a quadratic form in the row differences gets
+wrong by cancellation), scores against exact medians, slots against the serial
+recurrence on the same scores."""
 import pytest
 import torch
 
@@ -49,8 +50,8 @@ def _kappa64(h):
     return vals.mean(0) - 0.25 * vals.std(0, unbiased=False)
 
 
-# the quadratic forms add up to 40 times their value in absolute terms (independent
-# rows), each product of rows off by 2^-22: 1e-5 a form, 2e-5 for their quotient
+# kappa = 1 - cos: the dot product and the two norms each carry a few fp32 roundings of
+# their value, about 5e-7 together for |cos| <= 1 (4e-7 seen); the line lies at four times
 @pytest.mark.parametrize("T,Dh,n_seg,W", [(127, 40, 3, 16), (128, 32, 1, 16), (129, 264, 2, 1), (160, 8, 3, 8),
                                           (257, 72, 1, 37), (385, 4096, 1, 16), (500, 2048, 3, 16), (1031, 512, 3, 64),
                                           (70, 64, 8, 60), (90, 128, 3, 64), (33, 64, 1, 1), (4099, 1000, 2, 16)])
@@ -58,7 +59,7 @@ def test_curvature_tiles(T, Dh, n_seg, W):
     _, h, _, kappa, _, slots, N_c = _run(T, Dh, n_seg, W)
     err = float((kappa - _kappa64(h)).abs().max())
     print(f"T {T} Dh {Dh} n_seg {n_seg} N_c {N_c}: kappa off by {err:.2e}", flush=True)
-    assert err < 2e-5
+    assert err < 2e-6
     assert slots[-1] == N_c
 
 
@@ -77,7 +78,23 @@ def test_median_and_recurrence_changeover(T):
     assert slots == _run(T, 64, 1, serial=True)[5]
 
 
-# 768 row tiles: fewer share their columns among workgroups; the sums keep their order
+# rows h_t = base + (-1)^t swing + noise: every window mean lies near the base, so
+# kappa is well conditioned and window sums stay at a few fp32 roundings of it (1.1e-7
+# rms), while sums over differences d_t = +-2 swing with weights up to the window
+# cancel (1.1e-6 rms); the line lies at three times the former
+@pytest.mark.parametrize("Dh", [512, 2048, 4096])
+def test_curvature_of_alternating_rows(Dh):
+    T = 1200
+    gen = torch.Generator(device="cuda").manual_seed(Dh)
+    sign = 1.0 - 2.0 * (torch.arange(T, device="cuda") % 2)
+    base, swing = torch.randn(2, 3, 1, Dh, generator=gen, device="cuda")
+    h = (base + 0.7 * sign[None, :, None] * swing + 0.2 * torch.randn(3, T, Dh, generator=gen, device="cuda")).bfloat16()
+    err = (_run(T, Dh, 3, h=h)[3] - _kappa64(h)).pow(2).mean().sqrt()
+    print(f"Dh {Dh}: kappa off by {float(err):.2e} (rms)", flush=True)
+    assert err < 3e-7
+
+
+# the tile of a position does not depend on the length of the context, nor do its sums
 @pytest.mark.parametrize("T", [2000, 32640, 32768])
 def test_curvature_independent_of_the_context_length(T):
     h = _hidden(33000, 1024, 3, torch.Generator(device="cuda").manual_seed(3))
