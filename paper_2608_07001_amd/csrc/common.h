@@ -389,6 +389,14 @@ __device__ __forceinline__ float wave_max(float v) {
 // |x| 2^-24, the same order as the rounding already carried by x.
 __device__ __forceinline__ float fexp(float x) { return __builtin_amdgcn_exp2f(x * 1.44269504088896341f); }
 
+// s / n to the nearest float from inv = 1 / n to the nearest: the quotient's
+// remainder is exact.  (A key's mean with the reciprocal's error in every channel
+// moves its logits by that error times their size.)
+__device__ __forceinline__ float quotient(float s, float n, float inv) {
+  const float m = s * inv;
+  return fmaf(fmaf(-m, n, s), inv, m);
+}
+
 // Merge two (max, sum-of-exp) pairs: the sum is relative to its max.
 __device__ __forceinline__ void lse_merge(float& m, float& z, float m2, float z2) {
   float mn = fmaxf(m, m2);

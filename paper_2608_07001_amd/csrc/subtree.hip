@@ -369,24 +369,21 @@ __global__ __launch_bounds__(ST_T, 2) void k_subtree(const Dims* __restrict__ dm
           f32x4 acc[4], nn2 = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
           for (int pt = 0; pt < 4; ++pt) acc[pt] = f32x4{0.f, 0.f, 0.f, 0.f};
+          s16x8 kx[3][KS];
+          // the low parts first: the matrix cores truncate at the size of the sum so far
 #pragma unroll
-          for (int s = 0; s < KS; ++s) {
-            const uint16_t* src = sK + i16 * KPS + 32 * s + 8 * g4;
-            const s16x8 kh = pk8(*(const uint4*)src), km = pk8(*(const uint4*)(src + ST_N * KPS)),
-                        kl = pk8(*(const uint4*)(src + 2 * ST_N * KPS));
+          for (int part = 2; part >= 0; --part)
 #pragma unroll
-            for (int pt = 0; pt < 4; ++pt) {
-              const s16x8 qb = pk8(qf[pt][s]);
-              acc[pt] = mfma_bf16_16x16x32(kl, qb, acc[pt]);
-              acc[pt] = mfma_bf16_16x16x32(km, qb, acc[pt]);
-              acc[pt] = mfma_bf16_16x16x32(kh, qb, acc[pt]);
+            for (int s = 0; s < KS; ++s) {
+              kx[part][s] = pk8(*(const uint4*)(sK + (part * ST_N + i16) * KPS + 32 * s + 8 * g4));
+#pragma unroll
+              for (int pt = 0; pt < 4; ++pt) acc[pt] = mfma_bf16_16x16x32(kx[part][s], pk8(qf[pt][s]), acc[pt]);
             }
-            nn2 = mfma_bf16_16x16x32(kl, kh, nn2);
-            nn2 = mfma_bf16_16x16x32(kh, kl, nn2);
-            nn2 = mfma_bf16_16x16x32(km, km, nn2);
-            nn2 = mfma_bf16_16x16x32(km, kh, nn2);
-            nn2 = mfma_bf16_16x16x32(kh, km, nn2);
-            nn2 = mfma_bf16_16x16x32(kh, kh, nn2);
+#pragma unroll
+          for (int o = 0; o < 6; ++o) {
+            constexpr int pa[6] = {2, 0, 1, 1, 0, 0}, pb[6] = {0, 2, 1, 0, 1, 0};
+#pragma unroll
+            for (int s = 0; s < KS; ++s) nn2 = mfma_bf16_16x16x32(kx[pa[o]][s], kx[pb[o]][s], nn2);
           }
           mfma_done(nn2);
           mfma_done(acc);
@@ -396,9 +393,9 @@ __global__ __launch_bounds__(ST_T, 2) void k_subtree(const Dims* __restrict__ dm
             const float nch = (float)(i16 - a + 1);
             const float inv = __shfl(invn, (i16 - a) & 15, 64);
             const float km = sKn * inv + dm.eps;
-            const float me = fminf(fmaxf(nch * (ss * __builtin_amdgcn_rcpf(km * km)), 1.0f), nch);
+            const float me = fminf(fmaxf(nch * (ss / (km * km)), 1.0f), nch);
             const float beta = dm.beta_frac * sR * inv;
-            const float iden = __builtin_amdgcn_rcpf(sR + nch * beta + dm.eps);
+            const float iden = 1.0f / (sR + nch * beta + dm.eps);
             const float vv = (RR + beta * (2.f * RG + beta * GG)) * (iden * iden);
             if (past && g4 == (i16 >> 2)) sC[i16] = make_float4(beta, iden, vv, me);
           }
