@@ -92,16 +92,12 @@ TreeView make_view(void* base, const gracekv_plan& p) {
   // the lists of the refinement below the roots sit just before the kernel-argument copy
   const int64_t LG = p.unit_cap / p.J_cap;
   char* lv = b + p.tree_bytes - KARGS_BYTES - level_region_bytes(LG, p.N_c, p.unit_cap);
-  const int64_t cap = long_capacity(LG, p.N_c);
-  size_t o = 0;
-  auto take = [&](size_t bytes) { char* q = lv + o; o = (o + bytes + 255) & ~(size_t)255; return q; };
-  v.long_items[0] = (int32_t*)take((size_t)cap * 32);
-  v.long_items[1] = (int32_t*)take((size_t)cap * 32);
-  v.long_items[2] = (int32_t*)take((size_t)cap * 32);
-  v.long_cap = cap;
-  v.sub_items = (int32_t*)take((size_t)(LG * short_capacity(p.N_c)) * 32);
-  v.sub_ctr = (int32_t*)take((size_t)LG * 4);
-  v.lv_ctr = (int32_t*)take(64);
+  const BelowLists bl = below_lists(LG, p.N_c);
+  for (int c = 0; c < LONG_CLASSES; ++c) v.long_items[c] = (int32_t*)(lv + bl.long_items[c]);
+  v.long_cap = bl.long_cap;
+  v.sub_items = (int32_t*)(lv + bl.sub_items);
+  v.sub_ctr = (int32_t*)(lv + bl.sub_ctr);
+  v.lv_ctr = (int32_t*)(lv + bl.lv_ctr);
   return v;
 }
 
@@ -314,7 +310,7 @@ gracekv_status gracekv_plan_sizes(const gracekv_config* c, gracekv_plan* p) {
   put(p->off_theta, 16);
   put(p->off_selstate, selstate_bytes(dm));
   put(p->off_work, UC * 32);                // work items: 8 int32 each
-  put(p->off_wctr, 16);
+  put(p->off_wctr, 16 * 4);
   put(p->off_proto, UC * 2 * (size_t)c->d * (c->dtype == GRACEKV_BF16 ? 2 : 4));
   put(p->off_proto_logm, UC * 4);
   put(p->off_floor, c->alpha_floor > 0.0 ? floor_view(nullptr, dm, p->unit_cap, p->node_cap).bytes : 0);

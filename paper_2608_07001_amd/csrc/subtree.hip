@@ -28,16 +28,31 @@ namespace gkv {
 
 constexpr int ST_T = 256;                 // four waves, each on its own subtree
 
-// the nodes of a list are disjoint, of at least ST_N + 1 and 2 tokens
-int64_t long_capacity(int64_t LG, int64_t N_c) { return LG * (N_c / (ST_N + 1)) + 1; }
-
 static size_t al256(size_t x) { return (x + 255) & ~(size_t)255; }
 
-// Three lists of long nodes, the subtrees, their counters and lv_ctr, 22 bytes a
-// token; the region keeps the 40 that its interface version reserves.
+// The region of the lists: offsets of its arrays and its size, the one place that both
+// the plan and the view take them from.  The nodes of a list are disjoint, of at
+// least ST_N + 1 and 2 tokens: 22 bytes a token, and six roundings.
+BelowLists below_lists(int64_t LG, int64_t N_c) {
+  BelowLists b;
+  b.long_cap = LG * (N_c / (ST_N + 1)) + 1;
+  size_t o = 0;
+  auto put = [&](size_t& off, size_t bytes) { off = o; o = al256(o + bytes); };
+  for (int c = 0; c < LONG_CLASSES; ++c) put(b.long_items[c], (size_t)b.long_cap * 32);
+  put(b.sub_items, (size_t)(LG * short_capacity(N_c)) * 32);
+  put(b.sub_ctr, (size_t)LG * 4);
+  put(b.lv_ctr, 16 * 4);
+  b.bytes = o;
+  return b;
+}
+
+// The plan keeps at least the 40 bytes a token that its interface version reserves;
+// a few tokens' lists, whose arrays are all rounding, need more.
 size_t level_region_bytes(int64_t LG, int64_t N_c, int64_t unit_cap) {
   const size_t cap = (size_t)(LG * (N_c / 2) + 1);
-  return al256(cap * 32) + al256(cap * 48) + al256((size_t)unit_cap * 8) + al256((size_t)unit_cap * 16) + al256(64);
+  const size_t reserved = al256(cap * 32) + al256(cap * 48) + al256((size_t)unit_cap * 8) + al256((size_t)unit_cap * 16) + al256(64);
+  const size_t need = below_lists(LG, N_c).bytes;
+  return need > reserved ? need : reserved;
 }
 
 static __device__ __forceinline__ int uni(int v) { return __builtin_amdgcn_readfirstlane(v); }

@@ -43,3 +43,25 @@ def test_nodes_around_the_subtree_limit(d, hpg, W, k_curv, x):
     n = int(g["offsets"][-1])
     for k in ("pos_out", "logm_out", "K_out", "V_out"):
         assert torch.equal(g[k][:n], pr[k][:n]), k
+
+
+# contexts that leave a few tokens to compress: lists of one entry, whose arrays are all rounding
+@pytest.mark.parametrize("N_ctx,L,G", [(33, 1, 1), (34, 1, 1), (36, 2, 1), (40, 1, 1), (41, 1, 1), (36, 3, 1), (35, 2, 2),
+                                       (49, 1, 1), (50, 1, 2)])
+def test_contexts_of_a_few_tokens(N_ctx, L, G):
+    sh = small_shape(f"few-{N_ctx}-{L}-{G}", L=L, G=G, H=2 * G, d=64, N_ctx=N_ctx, W=4, dtype="bf16", x=1.0,
+                     n_segments=1, rope_base=5.0e5)
+    case = make_case(sh, 7, with_hidden=False)
+    kappa = make_kappa(sh, 7)
+    N_c = O.budget(L, G, N_ctx, 1.0).N_c
+    slots = [0] if N_c < 12 else [0, 5]
+    cd = H.to_dev(case)
+    for prune in (False, True):
+        g = H.gpu_run(cd, slots=slots, kappa=kappa, prune=prune)
+        if not prune:
+            H.parity(case, g, sh.name, slots=slots, kappa=kappa)
+        assert not H.validate_gpu_trees(g)
+        assert int(g["offsets"][-1]) == L * G * N_ctx
+        # all of the budget is spent on singletons: the cache itself
+        assert torch.equal(g["K_out"].view(L, G, N_ctx, 64), case["K"][:, :, :N_ctx])
+        assert torch.equal(g["V_out"].view(L, G, N_ctx, 64), case["V"][:, :, :N_ctx])
