@@ -469,13 +469,11 @@ __device__ __forceinline__ void split3x8(const float* x, uint4* part) {
 // compiler pads the wait for the matrix pipeline along one of the two paths into
 // the block only (seen where a wave-uniform branch follows the products: the
 // reader ran two cycles after them and took old values).  The wait is stated
-// here, in the products' own block; it covers every product issued before.
+// here, in the products' own block, with every accumulator that is read later as an
+// operand: a product may otherwise be scheduled behind it.
 __device__ __forceinline__ void mfma_done(f32x4& x) { asm volatile("s_nop 15\n\ts_nop 4" : "+v"(x)); }
-template <int N>
-__device__ __forceinline__ void mfma_done(f32x4 (&x)[N]) {
-  mfma_done(x[0]);
-#pragma unroll
-  for (int i = 1; i < N; ++i) asm volatile("" : "+v"(x[i]));
+__device__ __forceinline__ void mfma_done(f32x4 (&x)[4]) {
+  asm volatile("s_nop 15\n\ts_nop 4" : "+v"(x[0]), "+v"(x[1]), "+v"(x[2]), "+v"(x[3]));
 }
 
 // x[pt][r] (lane (i, g): row 4 g + r of a 16-row tile, column i of column tile
