@@ -113,18 +113,22 @@ __device__ __forceinline__ float group_sum(float v) {
   return col_sum4(v);
 }
 
-// Entries that a lane group folds in at once: two share one maximum and one
-// rescaling, but their rows and products take registers that waves in flight need.
-// Measured in us, one against two: fp32 33.9 -> 31.4 (five thousand to 131 K tokens
-// all gain or tie), but bf16 95.9 -> 108.6 for four heads of 64 and 239 -> 257 for
-// two of 128 at 32 K tokens and 4x, whose memory rate falls with the waves.
-__host__ __device__ constexpr int dec_block(bool bf16) { return bf16 ? 1 : 2; }
+// Entries that a lane group folds in at once.  Two share one maximum and one
+// rescaling, but their rows and products take registers (fp32, one to four heads: 66,
+// 86, 120 a lane with one entry, 108, 130, 167 with two) that waves in flight need.
+// Measured in us, one against two, for 256 rows of 32 K tokens at 4x, and 64 rows of
+// 8 K: fp32, one head 200.8 -> 193.2 and 29.3 -> 26.4, eight heads (few waves either
+// way) 403.5 -> 403.6 and 54.3 -> 49.7; but two heads 206 -> 220, four 234 -> 254
+// (31.2 -> 29.2 and 35.3 -> 34.7 where the rows leave the chip half idle), and bf16
+// 95.9 -> 108.6 for four heads of 64.
+__host__ __device__ constexpr int dec_block(bool bf16, int hpg) { return !bf16 && (hpg == 1 || hpg == 8) ? 2 : 1; }
 // Whether an entry past the end is skipped by a test, or takes part with the logit
-// -inf.  The test costs more where its branch splits many heads' work: eight heads
-// 309.8 -> 295.9 us without it (32 K tokens, 4x); four of 128 943.8 with, 951 without
-// (128 K).  A block of two has no one test.  The tested loop is kept apart: written
-// as a block of one it was 2.4 % slower for a short cache (64.8 -> 66.4 us).
-__host__ __device__ constexpr bool dec_test(bool bf16, int hpg) { return bf16 && hpg < 8; }
+// -inf.  The test costs more where its branch splits many heads' work: bf16, eight
+// heads 572 -> 553 us without it (256 rows of 32 K tokens at 4x); four of 128 943.8
+// with, 951 without (128 K).  A block of two has no one test.  The tested loop is
+// kept apart: written as a block of one it was 2.4 % slower for a short cache (64.8
+// -> 66.4 us).
+__host__ __device__ constexpr bool dec_test(bool bf16, int hpg) { return dec_block(bf16, hpg) == 1 && hpg < 8; }
 
 template <typename T, int D, int HPG>
 __global__ __launch_bounds__(DEC_T) void k_decode(Dims dm, int P, const T* __restrict__ q,
@@ -134,7 +138,7 @@ __global__ __launch_bounds__(DEC_T) void k_decode(Dims dm, int P, const T* __res
                                                   float2* __restrict__ pml, float* __restrict__ po) {
   constexpr int LPE = D / 8;                  // lanes per entry
   constexpr int EPW = 64 / LPE;               // entries per wave step
-  constexpr int EB = dec_block(sizeof(T) == 2);           // entries per lane group at a time
+  constexpr int EB = dec_block(sizeof(T) == 2, HPG);      // entries per lane group at a time
   constexpr bool TEST = dec_test(sizeof(T) == 2, HPG);
   constexpr float LOG2E = 1.44269504088896341f;
   __shared__ float sM[DEC_W][HPG], sS[DEC_W][HPG];
