@@ -162,9 +162,10 @@ __global__ __launch_bounds__(DEC_T) void k_decode(Dims dm, int P, const T* __res
 #pragma unroll
     for (int j = 0; j < 8; ++j) qv[h][j] *= sc2;
   }
-  // without the test, the least finite logit: a state that has seen nothing, or only
-  // an absent entry (logit -inf), stays (NONE, 0, 0)
-  constexpr float NONE = TEST ? -INFINITY : -FLT_MAX;
+  // the least finite logit: a state that has seen nothing, or only entries of the
+  // logit -inf (an absent one, or one that the caller masks by its log m), stays
+  // (NONE, 0, 0) instead of taking the difference of two infinities
+  constexpr float NONE = -FLT_MAX;
   float m[HPG], s[HPG], o[HPG][8];
 #pragma unroll
   for (int h = 0; h < HPG; ++h) {

@@ -84,3 +84,56 @@ def test_decode_on_the_oracle_packed_tiny_cache():
     want = O.decode_attention(H.np32(q), offsets, Ko, Vo, lm, H.np32(case["K"]), H.np32(case["V"]), sh.N_ctx, sh.G)
     worst = _compare(got, want)
     print(f"decode on the oracle's tiny cache: max rel err {worst:.2e}")
+
+
+FORMS = [("bf16", 128, 1), ("bf16", 128, 4), ("bf16", 64, 2), ("bf16", 128, 8), ("bf16", 64, 8), ("f32", 64, 1),
+         ("f32", 64, 2), ("f32", 64, 4), ("f32", 64, 8)]
+
+
+def _ragged(dtype, d, hpg, seed=5):
+    """A cache whose rows hold 0 to 300 entries (ranges that end inside a step), with its float64 attention."""
+    L, G, W = 2, 3, 5
+    cfg = gk.config_for(L=L, G=G, H=G * hpg, d=d, W=W, N_ctx=900, x=6.0, dtype=gk.BF16 if dtype == "bf16" else gk.F32,
+                        n_seg=1, D_hidden=64)
+    gen = torch.Generator().manual_seed(seed)
+    dt = torch.bfloat16 if dtype == "bf16" else torch.float32
+    B = gk.plan_sizes(cfg).B_total
+    cnt = torch.tensor([300, 1, 0, 129, 67, 33])
+    offsets = torch.cat([torch.zeros(1, dtype=torch.int64), cnt.cumsum(0)])
+    assert int(offsets[-1]) <= B
+    r = lambda *s: torch.randn(*s, generator=gen).to(dt)     # noqa: E731
+    pc = dict(offsets=offsets, K_out=r(B, d), V_out=r(B, d), logm_out=torch.rand(B, generator=gen) * 4)
+    return cfg, r(L, G * hpg, d) * 0.3, pc, r(L, G, 900 + W, d), r(L, G, 900 + W, d)
+
+
+def _attention64(cfg, q, pc, K, V):
+    out = torch.empty(q.shape, dtype=torch.float64)
+    at, hpg = pc["offsets"].tolist(), cfg.H // cfg.G
+    for i in range(cfg.L * cfg.G):
+        l, g = divmod(i, cfg.G)
+        k = torch.cat([pc["K_out"][at[i]:at[i + 1]], K[l, g, cfg.N_ctx:]]).double()
+        v = torch.cat([pc["V_out"][at[i]:at[i + 1]], V[l, g, cfg.N_ctx:]]).double()
+        lm = torch.cat([pc["logm_out"][at[i]:at[i + 1]].double(), torch.zeros(cfg.W, dtype=torch.float64)])
+        w = torch.softmax(q[l, g * hpg:(g + 1) * hpg].double() @ k.t() / cfg.d ** 0.5 + lm, -1)
+        out[l, g * hpg:(g + 1) * hpg] = (w[..., None] * torch.where(w[..., None] > 0, v, 0.0)).sum(1)
+    return out
+
+
+def _decode_cpu(cfg, q, pc, K, V):
+    return torch.from_numpy(_gpu_decode(cfg, q.cuda(), {k: x.cuda() for k, x in pc.items()}, K.cuda(), V.cuda())).double()
+
+
+def _close(got, want):
+    # fp32 sums of a few hundred terms and base-2 exponentials: the file's tolerance
+    return bool(((got - want).abs() <= RTOL * want.abs().amax(-1, keepdim=True) + 1e-6).all())
+
+
+@pytest.mark.parametrize("dtype,d,hpg", FORMS)
+def test_entries_masked_by_log_m(dtype, d, hpg):
+    # log m = -inf gives an entry no weight, wherever a lane group meets it: first, last, in all of its range
+    cfg, q, pc, K, V = _ragged(dtype, d, hpg)
+    for mask in (slice(0, 40), slice(100, 300), slice(300, 302), slice(301, 430), slice(0, None, 2), slice(1, None, 2),
+                 slice(0, None)):
+        p2 = dict(pc, logm_out=pc["logm_out"].clone())
+        p2["logm_out"][mask] = float("-inf")
+        assert _close(_decode_cpu(cfg, q, p2, K, V), _attention64(cfg, q, p2, K, V)), mask
