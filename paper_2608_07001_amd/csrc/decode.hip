@@ -22,6 +22,7 @@
 //     XCD on this chip, which costs far more than a second launch.)
 #include <cfloat>
 #include <mutex>
+#include <type_traits>
 
 #include "common.h"
 
@@ -114,23 +115,30 @@ __device__ __forceinline__ float group_sum(float v) {
 }
 
 // Entries that a lane group folds in at once.  Two share one maximum and one
-// rescaling, but their rows and products take registers (fp32, one to four heads: 66,
-// 86, 120 a lane with one entry, 108, 130, 167 with two) that waves in flight need.
-// Measured in us, one against two, for 256 rows of 32 K tokens at 4x, and 64 rows of
-// 8 K: fp32, one head 200.8 -> 193.2 and 29.3 -> 26.4, eight heads (few waves either
-// way) 403.5 -> 403.6 and 54.3 -> 49.7; but two heads 206 -> 220, four 234 -> 254
-// (31.2 -> 29.2 and 35.3 -> 34.7 where the rows leave the chip half idle), and bf16
-// 95.9 -> 108.6 for four heads of 64.
-__host__ __device__ constexpr int dec_block(bool bf16, int hpg) { return !bf16 && (hpg == 1 || hpg == 8) ? 2 : 1; }
+// rescaling, but their rows and products take registers (fp32, one, two and four
+// heads: 66, 86, 120 a lane with one entry, 108, 130, 167 with two) that waves in
+// flight need.  Measured in us, one against two:
+//   fp32, one head      200.8 -> 193.3 (256 rows of 32 K tokens at 4x), 29.3 -> 26.4 (64 of 8 K)
+//   fp32, eight heads   403.7 -> 398.5,  54.1 -> 48.4 (few waves either way)
+//   fp32, two heads     206.3 -> 219.5,  31.2 -> 29.2,  21.2 -> 20.1 (9 rows of 32 K)
+//   fp32, four heads    234.6 -> 254.1,  35.3 -> 34.7,  25.4 -> 24.4
+//   bf16, four heads of 64  95.9 -> 108.6
+// So two and four heads take two where the workgroups are few: the line lies between
+// 1088 (64 rows of 8 K tokens: a gain) and 1280 (256 of 2 K: four heads 26.4 -> 27.3).
+constexpr int64_t DEC_FEW = 1152;
+static int dec_block(bool bf16, int hpg, int64_t workgroups) {
+  if (bf16) return 1;
+  return hpg == 1 || hpg == 8 || workgroups <= DEC_FEW ? 2 : 1;
+}
 // Whether an entry past the end is skipped by a test, or takes part with the logit
 // -inf.  The test costs more where its branch splits many heads' work: bf16, eight
-// heads 572 -> 553 us without it (256 rows of 32 K tokens at 4x); four of 128 943.8
+// heads 572 -> 564 us without it (256 rows of 32 K tokens at 4x); four of 128 943.8
 // with, 951 without (128 K).  A block of two has no one test.  The tested loop is
 // kept apart: written as a block of one it was 2.4 % slower for a short cache (64.8
 // -> 66.4 us).
-__host__ __device__ constexpr bool dec_test(bool bf16, int hpg) { return dec_block(bf16, hpg) == 1 && hpg < 8; }
+__host__ __device__ constexpr bool dec_test(int block, int hpg) { return block == 1 && hpg < 8; }
 
-template <typename T, int D, int HPG>
+template <typename T, int D, int HPG, int EB>           // EB: entries per lane group at a time
 __global__ __launch_bounds__(DEC_T) void k_decode(Dims dm, int P, const T* __restrict__ q,
                                                   const int64_t* __restrict__ offsets, const T* __restrict__ Kout,
                                                   const T* __restrict__ Vout, const float* __restrict__ logm,
@@ -138,8 +146,7 @@ __global__ __launch_bounds__(DEC_T) void k_decode(Dims dm, int P, const T* __res
                                                   float2* __restrict__ pml, float* __restrict__ po) {
   constexpr int LPE = D / 8;                  // lanes per entry
   constexpr int EPW = 64 / LPE;               // entries per wave step
-  constexpr int EB = dec_block(sizeof(T) == 2, HPG);      // entries per lane group at a time
-  constexpr bool TEST = dec_test(sizeof(T) == 2, HPG);
+  constexpr bool TEST = dec_test(EB, HPG);
   constexpr float LOG2E = 1.44269504088896341f;
   __shared__ float sM[DEC_W][HPG], sS[DEC_W][HPG];
   __shared__ float sO[DEC_W][HPG][D];
@@ -232,8 +239,11 @@ __global__ __launch_bounds__(DEC_T) void k_decode(Dims dm, int P, const T* __res
     }
   } else {
     // EB entries per lane group at a time, the next ones in flight: one maximum and
-    // one rescaling of the running state for all of them.  Wave-uniform trip count;
-    // an entry past e1 contributes nothing.
+    // one rescaling of the running state for all of them.  Wave-uniform trip count.
+    // A range's last step may hold absent entries, past e1: they read entry e0's row
+    // in place of their own, with the logit -inf and, since 0 times an infinity is not
+    // 0, with the value 0 (that step is a copy of its own: a test in the loop cost
+    // eight heads 2 to 4 %).
     constexpr int64_t STEP = (int64_t)DEC_W * EPW * EB;
     Raw8<T> kn[EB], vn[EB];
     float lmn[EB];
@@ -251,7 +261,7 @@ __global__ __launch_bounds__(DEC_T) void k_decode(Dims dm, int P, const T* __res
     };
     const int64_t w0 = e0 + (int64_t)w * EPW * EB;
     if (w0 < e1) fetch(w0);
-    for (int64_t eb = w0; eb < e1; eb += STEP) {
+    auto fold = [&](int64_t eb, auto tail) {
       float kx[EB][8], vx[EB][8], lm[EB];
 #pragma unroll
       for (int b = 0; b < EB; ++b) {
@@ -259,7 +269,16 @@ __global__ __launch_bounds__(DEC_T) void k_decode(Dims dm, int P, const T* __res
         vn[b].get(vx[b]);
         lm[b] = lmn[b];
       }
-      if (eb + STEP < e1) fetch(eb + STEP);
+      if (decltype(tail)::value) {
+#pragma unroll
+        for (int b = 0; b < EB; ++b)
+          if (eb + b * EPW + row >= e1) {
+#pragma unroll
+            for (int j = 0; j < 8; ++j) vx[b][j] = 0.f;
+          }
+      } else if (eb + STEP < e1) {
+        fetch(eb + STEP);
+      }
 #pragma unroll
       for (int h = 0; h < HPG; ++h) {
         float x[EB];
@@ -285,7 +304,10 @@ __global__ __launch_bounds__(DEC_T) void k_decode(Dims dm, int P, const T* __res
           for (int j = 0; j < 8; ++j) o[h][j] += pe * vx[b][j];
         }
       }
-    }
+    };
+    int64_t eb = w0;
+    for (; eb + EPW * EB <= e1; eb += STEP) fold(eb, std::false_type{});
+    if (eb < e1) fold(eb, std::true_type{});
   }
   // merge the lane groups of the wave, then the waves
 #pragma unroll
@@ -390,20 +412,26 @@ hipError_t launch_decode(const Dims& dm, const void* q, const int64_t* offsets, 
   float2* pml = (float2*)ws;
   float* po = (float*)((char*)ws + al256(n * 8));
   const dim3 grid((unsigned)P, (unsigned)(dm.L * dm.G));
-#define GKV_DEC(TT, DD, HH)                                                                                    \
-  hipLaunchKernelGGL((k_decode<TT, DD, HH>), grid, dim3(DEC_T), 0, st, dm, P, (const TT*)q, offsets,          \
+  const int eb = dec_block(dm.dtype == GRACEKV_BF16, dm.hpg, (int64_t)P * dm.L * dm.G);
+#define GKV_DEC(TT, DD, HH, EE)                                                                                \
+  hipLaunchKernelGGL((k_decode<TT, DD, HH, EE>), grid, dim3(DEC_T), 0, st, dm, P, (const TT*)q, offsets,      \
                      (const TT*)K_out, (const TT*)V_out, logm_out, (const TT*)K, (const TT*)V, pml, po)
-#define GKV_DEC_H(TT, DD)                                                                                      \
+#define GKV_DEC_H(DD)                                                                                          \
   do {                                                                                                         \
-    if (dm.hpg == 1) GKV_DEC(TT, DD, 1); else if (dm.hpg == 2) GKV_DEC(TT, DD, 2);                             \
-    else if (dm.hpg == 4) GKV_DEC(TT, DD, 4); else if (dm.hpg == 8) GKV_DEC(TT, DD, 8);                       \
+    if (dm.hpg == 1) GKV_DEC(uint16_t, DD, 1, 1); else if (dm.hpg == 2) GKV_DEC(uint16_t, DD, 2, 1);           \
+    else if (dm.hpg == 4) GKV_DEC(uint16_t, DD, 4, 1); else if (dm.hpg == 8) GKV_DEC(uint16_t, DD, 8, 1);     \
     else return hipErrorInvalidValue;                                                                          \
   } while (0)
   if (dm.dtype == GRACEKV_BF16) {
-    if (dm.d == 128) GKV_DEC_H(uint16_t, 128); else if (dm.d == 64) GKV_DEC_H(uint16_t, 64);
+    if (dm.d == 128) GKV_DEC_H(128); else if (dm.d == 64) GKV_DEC_H(64);
     else return hipErrorInvalidValue;
   } else {
-    if (dm.d == 64) GKV_DEC_H(float, 64); else return hipErrorInvalidValue;
+    if (dm.d != 64) return hipErrorInvalidValue;
+    if (dm.hpg == 1) GKV_DEC(float, 64, 1, 2);
+    else if (dm.hpg == 2) { if (eb == 2) GKV_DEC(float, 64, 2, 2); else GKV_DEC(float, 64, 2, 1); }
+    else if (dm.hpg == 4) { if (eb == 2) GKV_DEC(float, 64, 4, 2); else GKV_DEC(float, 64, 4, 1); }
+    else if (dm.hpg == 8) GKV_DEC(float, 64, 8, 2);
+    else return hipErrorInvalidValue;
   }
 #undef GKV_DEC_H
 #undef GKV_DEC

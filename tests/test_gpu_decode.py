@@ -137,3 +137,52 @@ def test_entries_masked_by_log_m(dtype, d, hpg):
         p2 = dict(pc, logm_out=pc["logm_out"].clone())
         p2["logm_out"][mask] = float("-inf")
         assert _close(_decode_cpu(cfg, q, p2, K, V), _attention64(cfg, q, p2, K, V)), mask
+
+
+@pytest.mark.parametrize("hpg", [2, 4])
+def test_many_short_fp32_rows(hpg):
+    # more than a thousand workgroups: one entry at a time; the same rows as few workgroups take two
+    cfg, q, pc, K, V = _ragged("f32", 64, hpg)
+    L, G, reps = cfg.L, cfg.G, 180
+    few = _decode_cpu(cfg, q, pc, K, V)
+    many = gk.config_for(L=L * reps, G=G, H=cfg.H, d=64, W=cfg.W, N_ctx=900, x=6.0, dtype=gk.F32, n_seg=1, D_hidden=64)
+    B, n = gk.plan_sizes(many).B_total, int(pc["offsets"][-1])
+    step = n * torch.arange(reps)[:, None]
+    p2 = dict(offsets=torch.cat([(pc["offsets"][None, :-1] + step).flatten(), torch.tensor([n * reps])]))
+    for k in ("K_out", "V_out", "logm_out"):
+        x = torch.zeros((B,) + pc[k].shape[1:], dtype=pc[k].dtype)
+        x[:n * reps] = pc[k][:n].repeat((reps,) + (1,) * (x.dim() - 1))
+        p2[k] = x
+    got = _decode_cpu(many, q.repeat(reps, 1, 1), p2, K.repeat(reps, 1, 1, 1), V.repeat(reps, 1, 1, 1))
+    assert _close(few, _attention64(cfg, q, pc, K, V))
+    assert _close(got, few.repeat(reps, 1, 1))
+
+
+@pytest.mark.parametrize("dtype,d,hpg", FORMS)
+def test_infinite_values_stay_in_their_dimension(dtype, d, hpg):
+    # the first entry of every row (the one that lane groups past a range's end read in
+    # place of their own) holds an infinity: that dimension is infinite, the others are not
+    cfg, q, pc, K, V = _ragged(dtype, d, hpg)
+    pc["logm_out"][:] = 0.0
+    at, hit = pc["offsets"].tolist(), 0
+    for i in range(cfg.L * cfg.G):
+        if at[i + 1] > at[i]:
+            pc["V_out"][at[i], 5] = float("inf")
+            pc["V_out"][at[i], d - 3] = float("-inf")
+            hit += 1
+    got, want = _decode_cpu(cfg, q, pc, K, V), _attention64(cfg, q, pc, K, V)
+    assert torch.equal(torch.isfinite(got), torch.isfinite(want)) and int(torch.isinf(want).sum()) == 2 * hit * hpg
+    assert torch.equal(got[torch.isinf(want)], want[torch.isinf(want)])
+    fin = torch.isfinite(want)
+    assert _close(torch.where(fin, got, 0.0), torch.where(fin, want, 0.0))
+
+
+@pytest.mark.parametrize("dtype,d,hpg", FORMS)
+def test_rows_of_very_low_logits(dtype, d, hpg):
+    # equal keys and one huge negative logit everywhere (the window too): the plain mean of the values
+    cfg, q, pc, K, V = _ragged(dtype, d, hpg)
+    pc["K_out"][:] = 2.0 ** 50                  # powers of two: float64 sums them exactly, too
+    K[:] = 2.0 ** 50
+    pc["logm_out"][:] = 0.0
+    q = torch.full_like(q, -2.0 ** 50)
+    assert _close(_decode_cpu(cfg, q, pc, K, V), _attention64(cfg, q, pc, K, V))
