@@ -78,7 +78,10 @@ __host__ __device__ inline int64_t bt_chunks(int64_t N) { return (N + BTC - 1) /
 static size_t al(size_t x) { return (x + 255) & ~(size_t)255; }
 
 // The workspace.  The tables of the DP and the backtrack lie over dist2 and the
-// select state, which the slot scores were the last to read.
+// select state.  The slot scores have read those before, but for dist2's last row:
+// the terminal relaxation reads it again after the tables of the chunks' offsets
+// were written, and before those of the backtrack are.  seg_tables_fit holds the
+// layout to that.
 struct SegBytes {
   size_t kap9, sqd, sq, gram, dist2, bs, rz, P2, Poff, Fdbg, S, dp, smax, spare;
 };
@@ -116,7 +119,7 @@ static SegWs seg_view(void* ws, const Dims& dm) {
   s.sqd = (float*)p; p += b.sqd;
   s.sq = (float*)p; p += b.sq;
   s.gram = (float*)p; p += b.gram;
-  char* q = p;                               // DP and backtrack: at most dist2 + 2 bs + rz
+  char* q = p + (dm.N_c > 1 ? 0 : b.dist2);  // DP and backtrack (one token: its row is dist2's last)
   s.dlt = (long long*)q; q += al(C * 8);
   s.cdiff = (long long*)q; q += al(C * 8);
   s.cok = (int32_t*)q; q += al(C * 8);
@@ -133,6 +136,14 @@ static SegWs seg_view(void* ws, const Dims& dm) {
   s.Fg = (long long*)p; p += b.dp + b.spare;
   s.smax_part = (double*)p;
   return s;
+}
+
+static bool seg_tables_fit(const SegWs& s, const Dims& dm) {
+  const char* last = (const char*)(s.dist2 + (dm.N_c - 1) * BAND);      // dist2's last row
+  const char* off0 = (const char*)s.dlt;
+  const char* off1 = (const char*)s.bt_ent;                             // end of dlt, cdiff, cok
+  const bool apart = off1 <= last || off0 >= last + BAND * 4 || (dp_chunks(dm.N_c) == 1 && off0 + 8 <= last);   // one chunk: dlt[0] alone
+  return apart && (const char*)(s.bt_tab + bt_chunks(dm.N_c) * 128) <= (const char*)s.P2;
 }
 
 // Thread (p, q) owns the four positions i0 + 4p .. i0 + 4p + 3 and column quad
@@ -1167,6 +1178,7 @@ __global__ __launch_bounds__(64) void k_bt_emit(Dims dm, SegWs ws, int32_t* slot
 hipError_t launch_segment(const Dims& dm, const void* hidden, const float* surprisal, float* kappa, float* bscore,
                           int32_t* slot_starts, int32_t* n_slots, void* wsp, hipStream_t st) {
   SegWs ws = seg_view(wsp, dm);
+  if (dm.N_c > 0 && !seg_tables_fit(ws, dm)) return hipErrorInvalidValue;
   const dim3 g1((unsigned)((dm.T + CT - 1) / CT), dm.n_seg);
   // the Gram first: its diagonal gives the row norms of the curvature pass
   if (dm.dtype == GRACEKV_BF16) {

@@ -100,3 +100,18 @@ def test_curvature_independent_of_the_context_length(T):
     h = _hidden(33000, 1024, 3, torch.Generator(device="cuda").manual_seed(3))
     whole, part = _run(33000, 1024, 3, h=h)[3], _run(T, 1024, 3, h=h[:, :T].contiguous())[3]
     assert torch.equal(whole[:T - 16], part[:T - 16])
+
+
+@pytest.mark.parametrize("N_c", [1, 2, 3, 15, 16, 17])
+def test_contexts_of_a_few_tokens(N_c):
+    # one slot takes them all below n_min + 1, and the terminal relaxation finds it
+    gen = torch.Generator(device="cuda").manual_seed(N_c)
+    cfg = gk.config_for(L=1, G=1, H=1, d=64, W=3, N_ctx=32 + N_c, x=1.0, dtype=gk.BF16, n_seg=2, D_hidden=64)
+    buf = gk.allocate(cfg)
+    assert buf.plan.N_c == N_c
+    buf.seg_ws.fill_(0xFF)
+    T = buf.plan.T
+    h, s = _hidden(T, 64, 2, gen), torch.rand(T, generator=gen, device="cuda") * 8
+    gk.segment(cfg, h, s, buf.kappa, buf.bscore, buf.slot_starts, buf.n_slots, buf.seg_ws)
+    J = int(buf.n_slots.item())
+    assert buf.slot_starts[:J + 1].tolist() == [0, N_c]

@@ -2,7 +2,8 @@
 few tokens only and every array is rounding: a host program, compiled from the
 library's own header and linked with it, asks for the view of every small size and
 checks each array against the next and the kernel arguments at the end.  No GPU
-call is made."""
+call is made.  The same for the segmentation's workspace, where the tables of the
+recurrence lie over the distances that the slot scores have read."""
 import os
 import subprocess
 
@@ -69,13 +70,55 @@ int main() {
 """
 
 
-def test_arrays_do_not_overlap(tmp_path):
-    (tmp_path / "layout.hip").write_text(SRC)
-    exe = str(tmp_path / "layout")
-    subprocess.run([os.environ.get("HIPCC", "/opt/rocm/bin/hipcc"), "--offload-arch=gfx950", "--offload-host-only", "-O1",
-                    "-std=c++17", "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops", "-w",
-                    "-I", os.path.join(ROOT, "include"), "-I", os.path.join(PKG, "csrc"), str(tmp_path / "layout.hip"),
-                    "-o", exe, "-L", PKG, "-l:libgracekv.so", f"-Wl,-rpath,{PKG}"], check=True)
+SEG = r"""
+#include <stdio.h>
+#include "segment.hip"
+using namespace gkv;
+int main() {
+  int seen = 0, bad = 0;
+  for (int64_t N = 1; N < 1100000; N += N < 3000 ? 1 : N / 7 + 1)
+    for (int seg = 1; seg <= 3; seg += 2) {
+      Dims dm = {};
+      dm.N_c = N; dm.T = N + 40; dm.n_seg = seg; dm.Dh = 64; dm.n_min = 16; dm.n_max = 128;
+      char* base = (char*)0x100000;               // never dereferenced
+      const SegWs s = seg_view(base, dm);
+      const int64_t C = dp_chunks(N);
+      // what is live together: dist2's last row beside the offsets of all chunks (one chunk: its own only)
+      const char* last = (const char*)(s.dist2 + (N - 1) * BAND);
+      const char* lo = (const char*)s.dlt;
+      const char* hi = C > 1 ? (const char*)(s.cok + C) : (const char*)(s.dlt + 1);
+      const bool row = hi <= last || lo >= last + BAND * 4;
+      const bool order = (const char*)(s.dlt + C) <= (const char*)s.cdiff && (const char*)(s.cdiff + C) <= (const char*)s.cok &&
+                         (const char*)(s.cok + C) <= (const char*)s.bt_ent && (const char*)(s.bt_ent + bt_chunks(N)) <= (const char*)s.bt_tab &&
+                         (const char*)(s.bt_tab + bt_chunks(N) * 128) <= (const char*)s.P2;
+      const bool ends = (const char*)(s.Fg + C * (DPC + 128)) <= (const char*)s.smax_part &&
+                        (const char*)(s.smax_part + N / 16 + 2) <= base + segment_ws_bytes(dm);
+      ++seen;
+      if (!row || !order || !ends || !seg_tables_fit(s, dm)) {
+        if (bad++ < 8) printf("N_c %ld: row %d order %d ends %d check %d\n", (long)N, row, order, ends, (int)seg_tables_fit(s, dm));
+      }
+    }
+  printf("%d sizes, %d wrong\n", seen, bad);
+  return bad ? 1 : 0;
+}
+"""
+
+
+def _run(tmp_path, name, src, flags):
+    (tmp_path / f"{name}.hip").write_text(src)
+    exe = str(tmp_path / name)
+    subprocess.run([os.environ.get("HIPCC", "/opt/rocm/bin/hipcc"), "--offload-arch=gfx950", "-std=c++17", "-Xclang",
+                    "-target-feature", "-Xclang", "-packed-fp32-ops", "-w", "-I", os.path.join(ROOT, "include"),
+                    "-I", os.path.join(PKG, "csrc"), str(tmp_path / f"{name}.hip"), "-o", exe, "-L", PKG,
+                    "-l:libgracekv.so", f"-Wl,-rpath,{PKG}"] + flags, check=True)
     r = subprocess.run([exe], capture_output=True, text=True, timeout=120)
     assert r.returncode == 0, r.stdout[-2000:]
-    assert int(r.stdout.split()[0]) > 1000
+    return int(r.stdout.split()[0])
+
+
+def test_arrays_do_not_overlap(tmp_path):
+    assert _run(tmp_path, "layout", SRC, ["--offload-host-only", "-O1"]) > 1000
+
+
+def test_segmentation_tables_leave_live_distances(tmp_path):
+    assert _run(tmp_path, "segment_layout", SEG, ["-O1"]) > 5000
