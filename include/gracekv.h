@@ -212,7 +212,7 @@ gracekv_status gracekv_stage_times(float* total_ms, int32_t* launches);
  *   ws         workspace of plan.seg_ws_bytes bytes
  * The recurrence runs on slot scores rounded once to a common fixed-point grid
  * (a power-of-two step chosen from the largest |score|, finer than 1e-12 for
- * scores of order one), so its additions are exact; chunks of 1024 ends are
+ * scores of order one), so its additions are exact; chunks of 512 ends are
  * solved in parallel from a guessed state and accepted only where that is
  * provably exact, the rest is recomputed (GRACEKV_FLAG_DP_SERIAL recomputes
  * all of them).  Ties go to the smallest slot start. */

@@ -91,8 +91,8 @@ TreeView make_view(void* base, const gracekv_plan& p) {
   v.fl_state = nullptr;
   // the lists of the refinement below the roots sit just before the kernel-argument copy
   const int64_t LG = p.unit_cap / p.J_cap;
-  char* lv = b + p.tree_bytes - KARGS_BYTES - level_region_bytes(LG, p.N_c, p.unit_cap);
   const BelowLists bl = below_lists(LG, p.N_c);
+  char* lv = b + p.tree_bytes - KARGS_BYTES - bl.bytes;
   for (int c = 0; c < LONG_CLASSES; ++c) v.long_items[c] = (int32_t*)(lv + bl.long_items[c]);
   v.long_cap = bl.long_cap;
   v.sub_items = (int32_t*)(lv + bl.sub_items);
@@ -314,7 +314,7 @@ gracekv_status gracekv_plan_sizes(const gracekv_config* c, gracekv_plan* p) {
   put(p->off_proto, UC * 2 * (size_t)c->d * (c->dtype == GRACEKV_BF16 ? 2 : 4));
   put(p->off_proto_logm, UC * 4);
   put(p->off_floor, c->alpha_floor > 0.0 ? floor_view(nullptr, dm, p->unit_cap, p->node_cap).bytes : 0);
-  o += level_region_bytes(LG, p->N_c, p->unit_cap);       // lists of the refinement below the roots
+  o += below_lists(LG, p->N_c).bytes;        // lists of the refinement below the roots
   o += KARGS_BYTES;                          // device copy of the kernel arguments
   p->tree_bytes = o;
   p->seg_ws_bytes = segment_ws_bytes(dm);

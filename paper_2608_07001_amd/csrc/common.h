@@ -94,14 +94,12 @@ struct TreeView {
   int32_t* sub_ctr;     // [LG] their number
   int32_t* lv_ctr;      // [16] [c] long nodes of class c, [8 + c] next item of class c
 };
-// those lists: offsets in their region (256-byte steps), capacity of a long list, end of
-// the last array; and the bytes the plan gives the region
+// those lists: offsets in their region (256-byte steps), its size, capacity of a long list
 struct BelowLists {
   size_t long_items[LONG_CLASSES], sub_items, sub_ctr, lv_ctr, bytes;
   int64_t long_cap;
 };
 BelowLists below_lists(int64_t LG, int64_t N_c);
-size_t level_region_bytes(int64_t LG, int64_t N_c, int64_t unit_cap);
 __host__ __device__ inline int64_t short_capacity(int64_t N_c) { return N_c / 2; }   // per (l, g)
 
 // The singleton floor's region of the tree buffer (alpha_floor > 0).  Public

@@ -46,15 +46,6 @@ BelowLists below_lists(int64_t LG, int64_t N_c) {
   return b;
 }
 
-// The plan keeps at least the 40 bytes a token that its interface version reserves;
-// a few tokens' lists, whose arrays are all rounding, need more.
-size_t level_region_bytes(int64_t LG, int64_t N_c, int64_t unit_cap) {
-  const size_t cap = (size_t)(LG * (N_c / 2) + 1);
-  const size_t reserved = al256(cap * 32) + al256(cap * 48) + al256((size_t)unit_cap * 8) + al256((size_t)unit_cap * 16) + al256(64);
-  const size_t need = below_lists(LG, N_c).bytes;
-  return need > reserved ? need : reserved;
-}
-
 static __device__ __forceinline__ int uni(int v) { return __builtin_amdgcn_readfirstlane(v); }
 
 __global__ void k_sub_reset(const Dims* __restrict__ dmp, const TreeView* __restrict__ tvp) {

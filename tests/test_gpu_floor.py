@@ -120,15 +120,14 @@ def test_singleton_floor_matches_the_oracle(shape, seed, capped):
     assert over == capped
 
 
-def _level_region_bytes(p) -> int:
-    # after the floor's region: the level-by-level refinement lists (items of 32
-    # bytes and results of 48 for up to N_c / 2 nodes per (l, g), two unit lists,
-    # per-unit state of 16 bytes, 64 bytes of counters), each 256-byte aligned;
-    # then the 1024-byte copy of the kernel arguments
+def _lists_bytes(p) -> int:
+    # after the floor's region: the lists of the refinement below the roots (items of 32
+    # bytes: three lists of the nodes of 17 tokens and more, one of those of 2 to 16 per
+    # (l, g)), a counter per (l, g) and 64 bytes of counters, each 256-byte aligned; then
+    # the 1024-byte copy of the kernel arguments
     al = lambda x: (x + 255) // 256 * 256
     LG = p.unit_cap // p.J_cap
-    cap = LG * (p.N_c // 2) + 1
-    return al(cap * 32) + al(cap * 48) + al(p.unit_cap * 8) + al(p.unit_cap * 16) + al(64)
+    return 3 * al((LG * (p.N_c // 17) + 1) * 32) + al(LG * (p.N_c // 2) * 32) + al(LG * 4) + 256
 
 
 def test_floor_off_is_the_hot_path():
@@ -140,4 +139,4 @@ def test_floor_off_is_the_hot_path():
     for k in ("offsets", "K_out", "V_out", "pos_out", "logm_out"):
         assert torch.equal(a[k], b[k]), k
     p = b["plan"]
-    assert "floor" not in b and p.off_floor == p.tree_bytes - _level_region_bytes(p) - 1024
+    assert "floor" not in b and p.off_floor == p.tree_bytes - _lists_bytes(p) - 1024
